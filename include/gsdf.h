@@ -184,7 +184,11 @@ int gsdf_map_num_blocks(const gsdf_map* map, int32_t* n_dev, void* stream);
 int gsdf_allocate_blocks(gsdf_map* map, const float* depth_dev, const gsdf_camera* cam,
                          const double* T_wc_dev, int32_t* status_dev, void* stream);
 
-/* Scratch bytes gsdf_integrate_frame needs for `cam` (one float4 per pixel). */
+/* Scratch bytes gsdf_integrate_frame uses for `cam`: one float4 per pixel
+ * (rounded up to 256 bytes), then room for the partial sums of blocks that
+ * are fused in several parts.  With the pixels' share alone the call gives
+ * the same result, every block fused by one work-group (slower where
+ * surfaces are near the camera); with less it returns GSDF_EINVAL. */
 size_t gsdf_integrate_scratch_bytes(const gsdf_camera* cam);
 
 /* integrate_frame (Eq. (1)-(3)): for every valid pixel whose 5x5 normal fit
@@ -202,8 +206,7 @@ int gsdf_integrate_frame(gsdf_map* map, const float* depth_dev, const gsdf_camer
  * with the same results as the two calls in sequence, in two launches: the
  * allocation of each 16x16 pixel tile and the tile's normal fits share one
  * launch (neither reads what the other writes), then the per-block fusion.
- * Arguments as for gsdf_integrate_frame (scratch_dev: at least
- * gsdf_integrate_scratch_bytes(cam) bytes). */
+ * Arguments as for gsdf_integrate_frame. */
 int gsdf_fuse_frame(gsdf_map* map, const float* depth_dev, const gsdf_camera* cam, const double* T_wc_dev,
                     const gsdf_fuse_params* params, void* scratch_dev, size_t scratch_bytes,
                     int32_t* status_dev, void* stream);

@@ -14,17 +14,21 @@ constexpr int kAllocSet = 1024;  // LDS set capacity (keys) per tile
 // Tile (tu, tv): each pixel's ray band is mapped to block keys, collected in
 // the LDS set s_keys (neighbouring pixels share almost all of their
 // blocks); then every distinct key is inserted into the global table once
-// and marked as touched by this frame.  Every thread of the 256-thread
+// and marked as touched by this frame, by about the number of the tile's
+// pixels whose band meets the block (s_px).  Every thread of the 256-thread
 // work-group must call it (it synchronises); red holds 4 words of LDS.
 __device__ inline void allocate_tile(const MapView& M, const float* __restrict__ depth, int W, int H, float zmin,
                                      float zmax, const BandConsts& bc, const double* __restrict__ Twc,
                                      int32_t* status, int tu, int tv, unsigned long long* s_keys,
-                                     unsigned long long* red) {
+                                     int* s_px, unsigned long long* red) {
     if (!pose_finite(Twc)) {   // the same pose for every thread: a uniform exit
         if (tu == 0 && tv == 0 && threadIdx.x == 0) raise_status(status, GSDF_EINVAL);
         return;
     }
-    for (int i = threadIdx.x; i < kAllocSet; i += blockDim.x) s_keys[i] = kEmptyKey;
+    for (int i = threadIdx.x; i < kAllocSet; i += blockDim.x) {
+        s_keys[i] = kEmptyKey;
+        s_px[i] = 0;
+    }
     __syncthreads();
     const int u = tu * 16 + (threadIdx.x & 15);
     const int v = tv * 16 + (threadIdx.x >> 4);
@@ -34,6 +38,8 @@ __device__ inline void allocate_tile(const MapView& M, const float* __restrict__
                                            bc.Df, bc.nsamples);
         const float xr = pixel_xr(br, u);
         const float yr = pixel_yr(br, v);
+        // every fourth pixel counts for four
+        const bool counts = ((u | v) & 1) == 0;
         int pm[3] = {INT_MIN, INT_MIN, INT_MIN};
         int pb[3] = {INT_MIN, INT_MIN, INT_MIN};
         for (int k = 0; k < br.nsamples; ++k) {
@@ -56,6 +62,7 @@ __device__ inline void allocate_tile(const MapView& M, const float* __restrict__
                 const unsigned long long old = atomicCAS(&s_keys[h], kEmptyKey, key);
                 if (old == kEmptyKey || old == key) {
                     placed = true;
+                    if (counts) atomicAdd(&s_px[h], 4);
                     break;
                 }
                 h = (h + 1) & (kAllocSet - 1);
@@ -63,7 +70,7 @@ __device__ inline void allocate_tile(const MapView& M, const float* __restrict__
             if (!placed) {  // set full: go to the global table directly
                 int created;
                 const int32_t slot = hash_insert(M, bx, by, bz, status, &created);
-                if (slot >= 0) mark_touched(M, slot);
+                if (slot >= 0) mark_touched(M, slot, 1);
             }
         }
     }
@@ -76,7 +83,7 @@ __device__ inline void allocate_tile(const MapView& M, const float* __restrict__
         unpack_key(key, &bx, &by, &bz);
         // the inserting thread marks a new block; others mark known slots
         const int32_t slot = hash_insert(M, bx, by, bz, status, &created);
-        if (slot >= 0) mark_touched(M, slot);
+        if (slot >= 0) mark_touched(M, slot, max(s_px[i], 1));
         ++probes;
     }
     probes = block_sum_u64(probes, red);

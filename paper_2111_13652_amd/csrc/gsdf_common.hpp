@@ -122,13 +122,26 @@ __device__ inline unsigned short pack16(float f, int storage) {
 // Aux buffer layout (offsets in bytes from map.aux).
 struct AuxLayout {
     size_t block_keys;   // uint64 per pool slot
-    size_t counters;     // 64 int32
+    size_t counters;     // int32 words by Counter
     size_t stats;        // 16 uint64 work counters (cumulative since reset)
-    size_t touched_flag; // int32 per pool slot (per-frame touched marker)
+    size_t touched;      // int32 per pool slot: the frame's pixels that touch the block; whole chunks of 512
+    size_t split_done;   // kFuseTeams x kTeamBuffers int32: finished parts of a split block
     size_t total;
 };
 
-enum Counter { kNumBlocks = 0 };
+// The frame's touched blocks: per pool slot, the pixels whose band meets the
+// block (0: not touched; a block that another tile is still inserting counts
+// too few), from which fusion sizes its pieces.  Chunks of 64 slots belong to
+// kFuseTeams teams of work-groups in turn.  A team's tickets and its count of
+// finished work-groups sit 16 words apart (a device-scope atomic costs about
+// 44 ns on one address).
+constexpr int kFuseTeams = 8;
+constexpr int kMaxParts = 8;
+constexpr int kTeamBuffers = 256;               // partial-sum buffers of a team's split blocks
+__host__ __device__ inline size_t touched_slots(size_t nb) { return (nb + 511) / 512 * 512; }   // whole chunks of every team
+
+enum Counter { kNumBlocks = 0, kTeamTicket = 64, kTeamDone = kTeamTicket + kFuseTeams * 16,
+               kCounterWords = kTeamDone + kFuseTeams * 16 };
 
 // Work counters are striped over kStatStripes addresses (work-group b adds
 // into stripe b mod kStatStripes): device-scope atomics on one address
@@ -154,9 +167,10 @@ __host__ __device__ inline AuxLayout aux_layout(const gsdf_map_desc& d) {
     size_t nb = (size_t)d.max_blocks;
     size_t o = 0;
     a.block_keys = o;   o = align256(o + nb * 8);
-    a.counters = o;     o = align256(o + 64 * 4);
+    a.counters = o;     o = align256(o + kCounterWords * 4);
     a.stats = o;        o = align256(o + (size_t)kStatCount * kStatStripes * 8);
-    a.touched_flag = o; o = align256(o + nb * 4);
+    a.touched = o; o = align256(o + touched_slots(nb) * 4);
+    a.split_done = o;   o = align256(o + (size_t)kFuseTeams * kTeamBuffers * 4);
     a.total = o;
     return a;
 }
@@ -170,7 +184,8 @@ struct MapView {
     uint64_t* block_keys;
     int32_t* counters;
     unsigned long long* stats;
-    int32_t* touched_flag;
+    int32_t* touched;
+    int32_t* split_done;
     int32_t max_blocks;
     int32_t bounded;
     int32_t bmin[3], bmax[3];
@@ -191,7 +206,8 @@ inline MapView make_view(const gsdf_map& m) {
     v.block_keys = (uint64_t*)(aux + a.block_keys);
     v.counters = (int32_t*)(aux + a.counters);
     v.stats = (unsigned long long*)(aux + a.stats);
-    v.touched_flag = (int32_t*)(aux + a.touched_flag);
+    v.touched = (int32_t*)(aux + a.touched);
+    v.split_done = (int32_t*)(aux + a.split_done);
     v.max_blocks = (int32_t)m.desc.max_blocks;
     v.bounded = m.desc.bounded;
     for (int i = 0; i < 3; ++i) {
@@ -312,10 +328,11 @@ __device__ inline unsigned long long wave_sum_u64(unsigned long long x) {
     return x;
 }
 
-// Record that a block is touched by the current frame: an idempotent flag
-// (plain stores; the fusion kernel that consumes it runs later).
-__device__ inline void mark_touched(const MapView& M, int32_t slot) {
-    if (M.touched_flag[slot] == 0) M.touched_flag[slot] = 1;
+// Record that `pixels` more pixels of the current frame touch a block (the
+// fusion kernel that consumes the count runs later): a device-scope atomic
+// without a return, so nothing waits for it.
+__device__ inline void mark_touched(const MapView& M, int32_t slot, int pixels) {
+    __hip_atomic_fetch_add(&M.touched[slot], pixels, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Sum over a work-group (every thread passes its value; thread 0 gets the
@@ -404,6 +421,14 @@ __device__ inline bool band_sample(const BandRule& b, float xr, float yr, float 
         m[i] = (int)floorf(add_rn(mul_rn(q, b.invvs), 0.5f));
     }
     return true;
+}
+
+// floor(x) as an integer, one instruction (v_cvt_flr_i32_f32; a floor and a
+// conversion otherwise).
+__device__ inline int floor_int(float x) {
+    int r;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
 }
 
 __device__ inline float pixel_xr(const BandRule& b, int u) { return mul_rn(sub_rn((float)u, b.cxf), b.ifx); }

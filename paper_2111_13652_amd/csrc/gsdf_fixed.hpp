@@ -21,6 +21,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 
 namespace gsdf {
 
@@ -43,6 +44,29 @@ __host__ __device__ inline unsigned long long fixed_term(float ws, float wh, flo
     const float hs = floorf(wh * x);
     const float lo = fmaf(-hs, 4294967296.0f, s);
     return ((unsigned long long)(uint32_t)(int32_t)hs << 32) | (unsigned long long)sat_u32(lo);
+}
+
+// The same sums with terms formed in float64: t = fma(w, x, M) with
+// M = 1.5 * 2^(52-f) holds w x, rounded once to a multiple of 2^-f, in its low
+// mantissa bits (a float64 of that magnitude has no finer digits), so the
+// 64-bit difference of t's and M's bit patterns is the integer w x 2^f.  
+// |w x| < 2^(51-f).  A term costs an fma and a 64-bit addition (fixed_term:
+// six instructions), and the float64 product of two floats is exact.
+__host__ __device__ inline double magic_of(int f) { return ldexp(1.5, 52 - f); }
+
+__host__ __device__ inline unsigned long long double_bits(double t) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (unsigned long long)__double_as_longlong(t);
+#else
+    unsigned long long b;
+    std::memcpy(&b, &t, sizeof b);
+    return b;
+#endif
+}
+
+// t's integer, given the negated bit pattern of M
+__host__ __device__ inline unsigned long long magic_term(double t, unsigned long long neg_magic) {
+    return double_bits(t) + neg_magic;
 }
 
 __host__ __device__ inline float from_fixed(unsigned long long a, double inv) {

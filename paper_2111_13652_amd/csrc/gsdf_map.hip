@@ -102,8 +102,9 @@ __global__ __launch_bounds__(256) void k_allocate(MapView M, const float* __rest
                                                   int H, float zmin, float zmax, BandConsts bc,
                                                   const double* __restrict__ Twc, int32_t* status) {
     __shared__ unsigned long long s_keys[kAllocSet];
+    __shared__ int s_px[kAllocSet];
     __shared__ unsigned long long red[4];
-    allocate_tile(M, depth, W, H, zmin, zmax, bc, Twc, status, blockIdx.x, blockIdx.y, s_keys, red);
+    allocate_tile(M, depth, W, H, zmin, zmax, bc, Twc, status, blockIdx.x, blockIdx.y, s_keys, s_px, red);
 }
 
 __global__ void k_sum_stats(MapView M, unsigned long long* out) {
