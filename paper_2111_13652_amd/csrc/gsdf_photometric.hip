@@ -14,16 +14,23 @@
 // left increment of T_i [-a ; a x p_j], mapped through Jl(xi_i)^T.
 // The mean colour of Sec. 4.2 Eq. (21) uses the same visibility.
 //
-// Work layout: one work-group per map block, looping over the keyframes, so
-// each voxel's psi and colour gradients are summed in registers and written
-// once, without atomics; per keyframe the work-group's pose sums go to a
-// partial that a second kernel reduces in a fixed order.  Few of a block's
-// 512 voxels take part (those holding the surface: about 5 % on a room
-// map), so the work-group first lists them in voxel order and hands the
-// r-th to thread r mod 256 (two per thread at most): the projection and
-// sampling then run on dense lanes, and waves with nothing to do skip the
-// keyframe loop's work.  Projection and visibility are decided in float64 (they are
-// discrete decisions), samples and gradients are float32.
+// Work layout: one work-group per map block.  Few of a block's 512 voxels
+// take part (those holding the surface: about 5 % on a room map, 64 to 130 in
+// a block that has any), so the work-group first lists them in voxel order.
+// Then its four waves take the keyframes in turn, each with the listed voxels
+// on its lanes (two a lane, 128 together): a keyframe's pose sums stay within
+// a wave, which stores them as the block's partial without a barrier, and a
+// voxel's psi and colour gradients are summed in registers and, over the
+// waves, once in LDS before the voxel is written (no atomics).  A second
+// kernel reduces the partials in a fixed order.  Projection and visibility are
+// decided in float64 (they are discrete decisions), samples and gradients are
+// float32.
+//
+// Bound by the latency of a sample's chain (projection, depth, colours), which
+// wants waves in flight.  With the listed voxels spread over the work-group's
+// threads and all of it walking the keyframes together, one or two waves of
+// four worked, with two barriers a keyframe: loss and gradients of 30
+// keyframes at 640x480 took 247 us (kernel trace), now 99.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -38,6 +45,7 @@ namespace gsdf {
 constexpr int kPhotoBlock = 256;
 constexpr int kPhotoPart = 8;   // loss, 6 pose sums, visible count
 constexpr int kPhotoMaxKeyframes = 1024;
+constexpr int kPhotoBatch = 1;   // keyframes a wave takes between two barriers (2: the same time, twice the LDS)
 
 struct PhotoArgs {
     int32_t W, H, K, pad0;
@@ -85,7 +93,7 @@ __device__ inline void photo_voxel(const MapView& M, const PhotoArgs& a, const f
 
 // Projection of p into keyframe i (pose row-major 3x4); false when not seen.
 struct PhotoProj {
-    double x[3], z, u, v;
+    double x[3], z, iz, u, v;
 };
 
 __device__ inline bool photo_project(const PhotoArgs& a, const double* T, const float* __restrict__ depth_i,
@@ -94,8 +102,14 @@ __device__ inline bool photo_project(const PhotoArgs& a, const double* T, const 
     for (int r = 0; r < 3; ++r) P->x[r] = T[r] * d[0] + T[4 + r] * d[1] + T[8 + r] * d[2];
     P->z = P->x[2];
     if (!(P->z >= a.zmin)) return false;
-    P->u = a.fx * P->x[0] / P->z + a.cx;
-    P->v = a.fy * P->x[1] / P->z + a.cy;
+    // one reciprocal (hardware estimate and two Newton steps: within an ulp)
+    // for both quotients and the gradient's 1 / z
+    double iz = __builtin_amdgcn_rcp(P->z);
+    iz = fma(iz, fma(-P->z, iz, 1.0), iz);
+    iz = fma(iz, fma(-P->z, iz, 1.0), iz);
+    P->iz = iz;
+    P->u = fma(a.fx * P->x[0], iz, a.cx);
+    P->v = fma(a.fy * P->x[1], iz, a.cy);
     if (!(P->u >= 0.0 && P->u < (double)(a.W - 1) && P->v >= 0.0 && P->v < (double)(a.H - 1))) return false;
     const int iu = (int)floor(P->u + 0.5), iv = (int)floor(P->v + 0.5);
     const float D = depth_i[(size_t)iv * a.W + iu];
@@ -119,6 +133,32 @@ __device__ inline void bilinear3(const float* __restrict__ img, int W, double u,
     }
 }
 
+// Sums over a wave of kPhotoPart float64 values a lane: the pairwise tree of
+// lanes 32, 16, ... 1 apart, of which each of the first three steps keeps
+// half of the values (10 exchanges instead of 48, the same additions).
+// Returns value photo_part(lane).
+__device__ inline int photo_part(int lane) { return ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1); }
+
+__device__ inline double wave_sum_parts(const double (&d)[kPhotoPart], int lane) {
+    static_assert(kPhotoPart == 8, "three halvings");
+    double r4[4], r2[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const bool hi = lane & 32;
+        r4[i] = (hi ? d[4 + i] : d[i]) + __shfl_xor(hi ? d[i] : d[4 + i], 32);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const bool hi = lane & 16;
+        r2[i] = (hi ? r4[2 + i] : r4[i]) + __shfl_xor(hi ? r4[i] : r4[2 + i], 16);
+    }
+    const bool hi = lane & 8;
+    double r = (hi ? r2[1] : r2[0]) + __shfl_xor(hi ? r2[0] : r2[1], 8);
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) r += __shfl_xor(r, off);
+    return r;
+}
+
 // MODE 0: loss only; 1: loss and gradients; 2: mean colour (Eq. (21));
 // 3: adjoint of the mean colour: with the upstream gradient G_j (in
 // `colors`) and the view counts N_j (in `counts`), each sample adds
@@ -136,7 +176,8 @@ __global__ __launch_bounds__(kPhotoBlock) void k_photometric(MapView M, PhotoArg
                                                             const float* __restrict__ counts,
                                                             double* __restrict__ partials) {
     constexpr int kWaves = kPhotoBlock / 64;
-    __shared__ double s_red[kPhotoPart][kWaves];
+    // a batch's terms of each voxel: keyframes x voxels, two batches in turn
+    __shared__ float4 s_term[MODE == 0 ? 1 : 2][MODE == 0 ? 1 : kWaves * kPhotoBatch][MODE == 0 ? 1 : 2 * 64];
     __shared__ int s_wcount[2][kWaves];
     __shared__ short s_list[kBlockVoxels];
     const int64_t slot = blockIdx.x;
@@ -182,123 +223,137 @@ __global__ __launch_bounds__(kPhotoBlock) void k_photometric(MapView M, PhotoArg
                 partials[((size_t)(i / kPhotoPart) * a.param_blocks + slot) * kPhotoPart + i % kPhotoPart] = 0.0;
         return;
     }
-    // 2. thread t takes the listed voxels t and t + 256
-    PhotoVoxel V[2];
-    int vc[2];
-    for (int h = 0; h < 2; ++h) {
-        const int r = threadIdx.x + h * kPhotoBlock;
-        V[h].ok = false;
-        vc[h] = 0;
-        if (r >= n_act) continue;
-        vc[h] = s_list[r];
-        photo_voxel(M, a, params, MODE == 2 ? nullptr : colors, slot, vc[h], &V[h]);
-        if (MODE == 3) {
-            // upstream gradient per sample of the mean: G_j / N_j
-            const float n = counts[slot * kBlockVoxels + vc[h]];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) V[h].rho[c] /= n;
-        }
-    }
-    // waves holding a listed voxel (uniform per wave)
-    const bool any = wave * 64 < n_act;
+    // 2. 128 listed voxels at a time: on every wave, lane l takes l and l + 64
     const size_t npx = (size_t)a.W * a.H;
-    float gpsi[2] = {0.0f, 0.0f}, grho[2][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
-    float csum[2][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}}, cnt[2] = {0.0f, 0.0f};
-
-    for (int kf = 0; kf < a.K; ++kf) {
-        float acc[kPhotoPart];
+    for (int g = 0; g < n_act; g += 128) {
+        PhotoVoxel V[2];
+        int vc[2];
 #pragma unroll
-        for (int k = 0; k < kPhotoPart; ++k) acc[k] = 0.0f;
-        if (any) {
-            double T[12];
-            for (int i = 0; i < 12; ++i) T[i] = poses[12 * kf + i];
-            const float s = MODE == 1 ? gscale[kf] : 1.0f;
-            for (int h = 0; h < 2; ++h) {
-                if (!V[h].ok) continue;
-                PhotoProj P;
-                if (!photo_project(a, T, depth + kf * npx, V[h], &P)) continue;
-                float I[3], dIu[3], dIv[3];
-                bilinear3(rgb + 3 * kf * npx, a.W, P.u, P.v, I, dIu, dIv);
-                acc[7] += 1.0f;
-                if (MODE == 2) {
+        for (int h = 0; h < 2; ++h) {
+            const int r = g + lane + h * 64;
+            V[h].ok = false;
+            vc[h] = 0;
+            if (r >= n_act) continue;
+            vc[h] = s_list[r];
+            photo_voxel(M, a, params, MODE == 2 ? nullptr : colors, slot, vc[h], &V[h]);
+            if (MODE == 3) {
+                // upstream gradient per sample of the mean: G_j / N_j
+                const float n = counts[slot * kBlockVoxels + vc[h]];
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) csum[h][c] += I[c];
-                    cnt[h] += 1.0f;
-                    continue;
-                }
-                float eu = 0.0f, ev = 0.0f;
-                if (MODE == 3) {
+                for (int c = 0; c < 3; ++c) V[h].rho[c] /= n;
+            }
+        }
+        // thread r < 128: sums of listed voxel g + r.  MODE 2: colours and view
+        // count; else colour and psi gradients
+        float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        for (int k0 = 0, buf = 0; k0 < a.K; k0 += kWaves * kPhotoBatch, buf ^= 1) {
+            for (int j = 0; j < kPhotoBatch; ++j) {
+                const int kf = k0 + j * kWaves + wave;
+                if (kf >= a.K) break;
+                double part[kPhotoPart];
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        eu += V[h].rho[c] * dIu[c];
-                        ev += V[h].rho[c] * dIv[c];
+                for (int k = 0; k < kPhotoPart; ++k) part[k] = 0.0;
+                const double* T = poses + 12 * kf;
+                const float s = MODE == 1 ? gscale[kf] : 1.0f;
+                bool any = false;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (MODE != 0) s_term[buf][j * kWaves + wave][lane + h * 64] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    if (!V[h].ok) continue;
+                    PhotoProj P;
+                    if (!photo_project(a, T, depth + kf * npx, V[h], &P)) continue;
+                    any = true;
+                    float I[3], dIu[3], dIv[3];
+                    bilinear3(rgb + 3 * kf * npx, a.W, P.u, P.v, I, dIu, dIv);
+                    if (MODE == 2) {
+                        s_term[buf][j * kWaves + wave][lane + h * 64] = make_float4(I[0], I[1], I[2], 1.0f);
+                        continue;
+                    }
+                    part[7] += 1.0;
+                    float eu = 0.0f, ev = 0.0f, loss = 0.0f, drho[3] = {0.0f, 0.0f, 0.0f};
+                    if (MODE == 3) {
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            eu += V[h].rho[c] * dIu[c];
+                            ev += V[h].rho[c] * dIv[c];
+                        }
+                    }
+#pragma unroll
+                    for (int c = 0; c < 3 && MODE != 3; ++c) {
+                        const float r = I[c] - V[h].rho[c];
+                        const float ar = fabsf(r);
+                        const bool quad = ar <= a.delta;
+                        loss += a.lambda * (quad ? 0.5f * r * r : a.delta * (ar - 0.5f * a.delta));
+                        if (MODE == 1) {
+                            const float rp = s * a.lambda * (quad ? r : copysignf(a.delta, r));
+                            drho[c] = -rp;
+                            eu += rp * dIu[c];
+                            ev += rp * dIv[c];
+                        }
+                    }
+                    part[0] += (double)loss;
+                    if (MODE == 1 || MODE == 3) {
+                        const float iz = (float)P.iz;
+                        const float fx = (float)a.fx, fy = (float)a.fy;
+                        const float x0 = (float)P.x[0], x1 = (float)P.x[1];
+                        const float gx[3] = {eu * fx * iz, ev * fy * iz, -(eu * fx * x0 + ev * fy * x1) * iz * iz};
+                        float aw[3];
+#pragma unroll
+                        for (int r = 0; r < 3; ++r)
+                            aw[r] = (float)T[4 * r] * gx[0] + (float)T[4 * r + 1] * gx[1] + (float)T[4 * r + 2] * gx[2];
+                        s_term[buf][j * kWaves + wave][lane + h * 64] =
+                            make_float4(drho[0], drho[1], drho[2],
+                                        -(aw[0] * V[h].ghf[0] + aw[1] * V[h].ghf[1] + aw[2] * V[h].ghf[2]));
+                        const float p0 = (float)V[h].p[0], p1 = (float)V[h].p[1], p2 = (float)V[h].p[2];
+                        part[1] -= (double)aw[0];
+                        part[2] -= (double)aw[1];
+                        part[3] -= (double)aw[2];
+                        part[4] += (double)(aw[1] * p2 - aw[2] * p1);
+                        part[5] += (double)(aw[2] * p0 - aw[0] * p2);
+                        part[6] += (double)(aw[0] * p1 - aw[1] * p0);
                     }
                 }
-#pragma unroll
-                for (int c = 0; c < 3 && MODE != 3; ++c) {
-                    const float r = I[c] - V[h].rho[c];
-                    const float ar = fabsf(r);
-                    const bool quad = ar <= a.delta;
-                    acc[0] += a.lambda * (quad ? 0.5f * r * r : a.delta * (ar - 0.5f * a.delta));
-                    if (MODE == 1) {
-                        const float rp = s * a.lambda * (quad ? r : copysignf(a.delta, r));
-                        grho[h][c] -= rp;
-                        eu += rp * dIu[c];
-                        ev += rp * dIv[c];
-                    }
+                if (MODE == 2) continue;
+                // the keyframe's sums over this block's voxels
+                const double x = __any(any) ? wave_sum_parts(part, lane) : 0.0;
+                if ((lane & 7) == 0) {
+                    double* out = partials + ((size_t)kf * a.param_blocks + slot) * kPhotoPart + photo_part(lane);
+                    *out = g == 0 ? x : *out + x;   // the same lane stored it
                 }
-                if (MODE == 1 || MODE == 3) {
-                    const float iz = (float)(1.0 / P.z);
-                    const float fx = (float)a.fx, fy = (float)a.fy;
-                    const float x0 = (float)P.x[0], x1 = (float)P.x[1];
-                    const float gx[3] = {eu * fx * iz, ev * fy * iz, -(eu * fx * x0 + ev * fy * x1) * iz * iz};
-                    float aw[3];
+            }
+            if (MODE == 0) continue;
+            __syncthreads();
+            if (threadIdx.x < 128) {
 #pragma unroll
-                    for (int r = 0; r < 3; ++r)
-                        aw[r] = (float)T[4 * r] * gx[0] + (float)T[4 * r + 1] * gx[1] + (float)T[4 * r + 2] * gx[2];
-                    gpsi[h] -= aw[0] * V[h].ghf[0] + aw[1] * V[h].ghf[1] + aw[2] * V[h].ghf[2];
-                    const float p0 = (float)V[h].p[0], p1 = (float)V[h].p[1], p2 = (float)V[h].p[2];
-                    acc[1] -= aw[0];
-                    acc[2] -= aw[1];
-                    acc[3] -= aw[2];
-                    acc[4] += aw[1] * p2 - aw[2] * p1;
-                    acc[5] += aw[2] * p0 - aw[0] * p2;
-                    acc[6] += aw[0] * p1 - aw[1] * p0;
+                for (int j = 0; j < kWaves * kPhotoBatch; ++j) {
+                    if (k0 + j >= a.K) break;
+                    const float4 t = s_term[buf][j][threadIdx.x];
+                    sum.x += t.x;
+                    sum.y += t.y;
+                    sum.z += t.z;
+                    sum.w += t.w;
                 }
             }
         }
-        if (MODE == 2) continue;
-        // work-group sums for this keyframe (float64 across lanes)
-#pragma unroll
-        for (int k = 0; k < kPhotoPart; ++k) {
-            double x = (double)acc[k];
-            if (any)
-                for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-            if (lane == 0) s_red[k][wave] = x;
+        const int r = g + threadIdx.x;
+        if (MODE != 0 && threadIdx.x < 128 && r < n_act) {
+            const int64_t vi = slot * kBlockVoxels + s_list[r];
+            if (MODE == 2) {
+                const float n = sum.w;
+                out_colors[3 * vi] = n > 0.0f ? sum.x / n : 0.0f;
+                out_colors[3 * vi + 1] = n > 0.0f ? sum.y / n : 0.0f;
+                out_colors[3 * vi + 2] = n > 0.0f ? sum.z / n : 0.0f;
+                if (out_count) out_count[vi] = n;
+            } else {
+                dparams[4 * vi] += sum.w;
+                if (MODE == 1) {
+                    dcolors[3 * vi] += sum.x;
+                    dcolors[3 * vi + 1] += sum.y;
+                    dcolors[3 * vi + 2] += sum.z;
+                }
+            }
         }
-        __syncthreads();
-        if (threadIdx.x < kPhotoPart) {
-            double x = 0.0;
-            for (int w = 0; w < kPhotoBlock / 64; ++w) x += s_red[threadIdx.x][w];
-            partials[((size_t)kf * a.param_blocks + slot) * kPhotoPart + threadIdx.x] = x;
-        }
-        __syncthreads();
-    }
-    for (int h = 0; h < 2; ++h) {
-        if (!V[h].ok) continue;
-        const int64_t vi = slot * kBlockVoxels + vc[h];
-        if (MODE == 2) {
-            const float n = cnt[h];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) out_colors[3 * vi + c] = n > 0.0f ? csum[h][c] / n : 0.0f;
-            if (out_count) out_count[vi] = n;
-        } else if (MODE == 1) {
-            dparams[4 * vi] += gpsi[h];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) dcolors[3 * vi + c] += grho[h][c];
-        } else if (MODE == 3) {
-            dparams[4 * vi] += gpsi[h];
-        }
+        __syncthreads();   // the terms are written again for the next voxels
     }
 }
 
