@@ -47,13 +47,16 @@ constexpr int kAdjBlock = 256;
 constexpr int kAdjPart = 8;         // doubles per work-group partial: loss, 6 pose sums, count
 constexpr int kAdjMaxGroups = 512;  // work-groups per keyframe of the pixel passes
 constexpr int kAdjTile = 32;        // the pixel passes take 32x32 pixel tiles, four pixels a thread
-constexpr int kBackGroups = 8192;   // work-groups of the per-block gather (each owns every 8192th block)
-constexpr int kScanTile = 4096;     // block counts per work-group of the offset scan (16 a thread)
-constexpr int kPoseLds = 64;        // the gather keeps the poses in LDS for up to this many keyframes
+constexpr int kScanTile = 4096;     // block counts per work-group of the offset scan
+constexpr int kScanBlock = 1024;    // threads of the offset scan
 constexpr int kTilePx = kAdjTile * kAdjTile;
-constexpr int kGatherBatch = 2;     // list entries a thread of the gather loads at a time
+constexpr int kGatherBatch = 2;     // list entries a lane of the gather loads at a time
 constexpr int kLookup = 2;          // pixels a thread of the pixel passes looks up together
-constexpr int kRunBatch = 256;      // runs the gather holds in LDS at a time
+// Pixels to a piece of the gather: a 2048th of the pixels of all keyframes (two
+// pieces for each of the chip's resident work-groups), at least kMinPiece.  A
+// block with more than twice that is gathered in parts.
+constexpr int kGatherShare = 2048;
+constexpr int kMinPiece = 1024;
 
 struct AdjArgs {
     int32_t W, H, groups, freeze;
@@ -66,14 +69,20 @@ struct AdjArgs {
 // Scratch of the keyframe calls: per-work-group partials of the keyframe
 // sums, the keyframe poses exp(xi^) T0, two words of bounds (the reach of a
 // frozen association as float64 bits, max |s_i|), and the pixel lists:
-// per tile (K x tiles of them) 1024 list entries (pixel id, depth) and up
+// per tile (K x tiles of them) 1024 list entries (pixel of the tile, depth) and up
 // to 1024 records
 // (block, count), the records' count per tile, the runs (start, count)
 // sorted by block, and per block its pixel count, run count, first run and
-// a cursor, with the per-tile sums of the scan.
+// a cursor, with the per-tile sums of the scan.  Then what the gather needs to
+// take a block in parts.
 struct AdjScratch {
     size_t partials, poses, bounds, list, recs, nrec, runs, pix_count, run_count, run_off, cursor, tiles, total;
+    // the gather's pieces (a caller whose scratch ends at `total` has every
+    // block gathered whole)
+    size_t tile_sums, items, done, buffers, split_total;
+    int32_t piece, n_buffers;   // pixels to a piece; partial-sum buffers
 };
+constexpr size_t kBufferBytes = (size_t)4 * kBlockVoxels * sizeof(unsigned long long);
 
 inline int64_t adj_tiles(int32_t W, int32_t H) {
     return (int64_t)((W + kAdjTile - 1) / kAdjTile) * ((H + kAdjTile - 1) / kAdjTile);
@@ -98,6 +107,17 @@ inline AdjScratch adj_scratch(int32_t K, int64_t tiles, int64_t param_blocks) {
     L.cursor = o;    o = align256(o + nb * sizeof(int32_t));
     L.tiles = o;     o = align256(o + ((nb + kScanTile - 1) / kScanTile) * sizeof(int32_t));
     L.total = o;
+    const int64_t piece = (int64_t)(n / kGatherShare);
+    L.piece = (int32_t)(piece > kMinPiece ? piece : kMinPiece);
+    // blocks above two pieces: at most n / (2 piece) of them, with n / piece
+    // whole pieces between them and one more each (and room for the rounding
+    // of the quotients)
+    L.n_buffers = (int32_t)(2 * (int64_t)n / (int64_t)L.piece + 2);
+    L.tile_sums = o; o = align256(o + ((nb + kScanTile - 1) / kScanTile) * 2 * sizeof(int32_t));
+    L.items = o;     o = align256(o + (nb + (size_t)L.n_buffers + 1) * sizeof(int4));
+    L.done = o;      o = align256(o + nb * sizeof(int32_t));
+    L.buffers = o;   o = align256(o + (size_t)L.n_buffers * kBufferBytes);
+    L.split_total = o;
     return L;
 }
 
@@ -344,7 +364,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_keyframe_loss(MapView M, AdjArgs 
 __global__ void k_adj_setup(int32_t K, const double* __restrict__ T0, const double* __restrict__ xi,
                             double* __restrict__ poses, int64_t nb, int32_t* __restrict__ pix_count,
                             int32_t* __restrict__ run_count, int32_t* __restrict__ cursor,
-                            unsigned long long* __restrict__ reach) {
+                            int32_t* __restrict__ done, unsigned long long* __restrict__ reach) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < K) {
         double pose[12];
@@ -356,17 +376,20 @@ __global__ void k_adj_setup(int32_t K, const double* __restrict__ T0, const doub
         pix_count[i] = 0;
         run_count[i] = 0;
         cursor[i] = 0;
+        if (done) done[i] = 0;
     }
     if (i == 0 && reach) *reach = 0ull;
 }
 
-// Exclusive work-group prefix sums of two int32 per thread (all 256
-// threads): a wave scan, the wave totals in LDS (s_w: 8 words).  The
+// Exclusive work-group prefix sums of two int32 per thread (all threads of
+// WAVES waves): a wave scan, the wave totals in LDS (s_w: 2 WAVES words).  The
 // totals land in *tot_a, *tot_b.
+template <int WAVES = 4>
 __device__ inline void block_scan2(int32_t a, int32_t b, int32_t* ex_a, int32_t* ex_b, int32_t* tot_a,
                                    int32_t* tot_b, int32_t* s_w) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int32_t ia = a, ib = b;
+#pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
         const int32_t ya = __shfl_up(ia, d), yb = __shfl_up(ib, d);
         if (lane >= d) {
@@ -377,18 +400,18 @@ __device__ inline void block_scan2(int32_t a, int32_t b, int32_t* ex_a, int32_t*
     __syncthreads();   // s_w may still be read by a previous call
     if (lane == 63) {
         s_w[wave] = ia;
-        s_w[4 + wave] = ib;
+        s_w[WAVES + wave] = ib;
     }
     __syncthreads();
     int32_t pa = 0, pb = 0, ta = 0, tb = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
         if (w < wave) {
             pa += s_w[w];
-            pb += s_w[4 + w];
+            pb += s_w[WAVES + w];
         }
         ta += s_w[w];
-        tb += s_w[4 + w];
+        tb += s_w[WAVES + w];
     }
     *ex_a = pa + ia - a;
     *ex_b = pb + ib - b;
@@ -404,7 +427,7 @@ __device__ inline void block_scan2(int32_t a, int32_t b, int32_t* ex_a, int32_t*
 // usable pixels are grouped by block in LDS (an open-addressing table of
 // 1024 entries, so it never fills; one LDS atomic add gives a pixel its
 // rank in its block); a scan of the entries' counts places each block's
-// pixels (id and depth) in a run of the region's 1024 list entries, and the region gets
+// pixels (place in the tile and depth) in a run of the region's 1024 list entries, and the region gets
 // one record (block, count) per block, in run order, and nrec[r] records.
 // The per-block pixel and record counts are integer atomics.  With a
 // frozen association the pass also finds how far (per axis, metres) the
@@ -479,7 +502,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_adj_pixels(MapView M, AdjArgs a, 
             for (int j = 0; j < kLookup; ++j) {
                 ent[g + j] = -1;
                 rank[g + j] = 0;
-                pid[g + j] = (uint32_t)((size_t)kf * N + (size_t)v[j] * a.W + u[j]);
+                pid[g + j] = threadIdx.x + (g + j) * kAdjBlock;
                 dep[g + j] = P[j].D;
                 if (!ok[j]) continue;
                 const ResidualTerms rt = residual_terms(P[j], a.delta, s);
@@ -547,67 +570,145 @@ __global__ __launch_bounds__(kAdjBlock) void k_adj_pixels(MapView M, AdjArgs a, 
     }
 }
 
-// Work-group sum of one int32 per thread (all 256 threads), in every thread.
+// Work-group sum of one int32 per thread (all threads of WAVES waves), in
+// every thread.
+template <int WAVES>
 __device__ inline int32_t block_sum_i32(int32_t x, int32_t* s_w) {
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = x;
     __syncthreads();
-    return s_w[0] + s_w[1] + s_w[2] + s_w[3];
+    int32_t t = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) t += s_w[w];
+    return t;
 }
 
-// Sum of the per-block run counts of each tile of kScanTile blocks.
+// Parts in which a block of n pixels in `runs` runs is gathered.
+__device__ inline int32_t gather_parts(int32_t n, int32_t runs, int32_t piece, float inv_piece) {
+    if (piece == 0 || n <= 2 * piece) return 1;
+    const int32_t p = (int32_t)((float)n * inv_piece) + 1;
+    return p < runs ? p : runs;
+}
+
+// Sums over each tile of kScanTile blocks: run counts, and with pieces the
+// blocks that have pixels and the parts of those that are split.
 __global__ __launch_bounds__(256) void k_adj_tile_sums(int64_t nb, const int32_t* __restrict__ counts,
-                                                       int32_t* __restrict__ tiles) {
+                                                       const int32_t* __restrict__ pix_count, int32_t piece,
+                                                       int32_t* __restrict__ tiles, int32_t* __restrict__ piece_tiles) {
     __shared__ int32_t s_w[4];
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    int32_t x = 0;
+    int32_t x = 0, blocks = 0, parts = 0;
     for (int k = threadIdx.x; k < kScanTile; k += 256)
-        if (base + k < nb) x += counts[base + k];
-    x = block_sum_i32(x, s_w);
+        if (base + k < nb) {
+            const int32_t r = counts[base + k];
+            x += r;
+            if (piece && r > 0) {
+                const int32_t p = gather_parts(pix_count[base + k], r, piece, 1.0f / (float)piece);
+                if (p > 1)
+                    parts += p;
+                else
+                    ++blocks;
+            }
+        }
+    x = block_sum_i32<4>(x, s_w);
     if (threadIdx.x == 0) tiles[blockIdx.x] = x;
+    if (!piece) return;
+    blocks = block_sum_i32<4>(blocks, s_w);
+    parts = block_sum_i32<4>(parts, s_w);
+    if (threadIdx.x == 0) {
+        piece_tiles[2 * blockIdx.x] = blocks;
+        piece_tiles[2 * blockIdx.x + 1] = parts;
+    }
 }
 
 // First run of each block (exclusive prefix sums of the run counts), one
 // work-group per tile: the sum of the earlier tiles, then a scan of the
-// tile (16 consecutive counts a thread).  Work-group 0 also writes
-// max_i |s_i|.
-__global__ __launch_bounds__(256) void k_adj_offsets(int64_t nb, const int32_t* __restrict__ counts,
+// tile (four consecutive counts a thread).  With pieces also the list of the
+// gather's items {slot, part, parts, first buffer}: at 1 + i the i-th part of
+// a split block (buffer i), then from 1 + (all parts) on the whole blocks
+// that have pixels; item 0 holds {all parts, whole blocks} (each written by
+// the tile that knows it).  Work-group 0 also writes max_i |s_i|.
+__global__ __launch_bounds__(kScanBlock) void k_adj_offsets(int64_t nb, const int32_t* __restrict__ counts,
                                                      const int32_t* __restrict__ tiles,
                                                      int32_t* __restrict__ offsets, int32_t K,
-                                                     const float* __restrict__ gscale, double* __restrict__ bounds) {
-    __shared__ int32_t s_w[8];
-    int32_t before = 0;
+                                                     const float* __restrict__ gscale, double* __restrict__ bounds,
+                                                     const int32_t* __restrict__ pix_count, int32_t piece,
+                                                     const int32_t* __restrict__ piece_tiles,
+                                                     int4* __restrict__ items) {
+    constexpr int kWaves = kScanBlock / 64, kPer = kScanTile / kScanBlock;
+    __shared__ int32_t s_w[2 * kWaves];
+    int32_t before = 0, before_blocks = 0, before_parts = 0, all_parts = 0;
     if (tiles) {   // null for a single tile
-        for (int g = threadIdx.x; g < (int)blockIdx.x; g += 256) before += tiles[g];
-        before = block_sum_i32(before, s_w);
+        for (int g = threadIdx.x; g < (int)blockIdx.x; g += kScanBlock) before += tiles[g];
+        before = block_sum_i32<kWaves>(before, s_w);
+        if (piece) {
+            for (int g = threadIdx.x; g < (int)gridDim.x; g += kScanBlock) {
+                if (g < (int)blockIdx.x) {
+                    before_blocks += piece_tiles[2 * g];
+                    before_parts += piece_tiles[2 * g + 1];
+                }
+                all_parts += piece_tiles[2 * g + 1];
+            }
+            before_blocks = block_sum_i32<kWaves>(before_blocks, s_w);
+            before_parts = block_sum_i32<kWaves>(before_parts, s_w);
+            all_parts = block_sum_i32<kWaves>(all_parts, s_w);
+        }
     }
-    const int64_t i0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * 16;
-    int32_t c[16];
+    const int64_t i0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kPer;
+    int32_t c[kPer];
     int32_t own = 0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
+    for (int k = 0; k < kPer; ++k) {
         c[k] = i0 + k < nb ? counts[i0 + k] : 0;
         own += c[k];
     }
     int32_t run, unused, tot, tot2;
-    block_scan2(own, 0, &run, &unused, &tot, &tot2, s_w);
+    block_scan2<kWaves>(own, 0, &run, &unused, &tot, &tot2, s_w);
     run += before;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
+    for (int k = 0; k < kPer; ++k) {
         if (i0 + k < nb) offsets[i0 + k] = run;
         run += c[k];
     }
+    if (piece) {
+        int32_t p[kPer], blocks = 0, parts = 0;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            p[k] = c[k] > 0 ? gather_parts(pix_count[i0 + k], c[k], piece, 1.0f / (float)piece) : 0;
+            if (p[k] > 1)
+                parts += p[k];
+            else
+                blocks += p[k];
+        }
+        int32_t at_block, at_part, tot_blocks, tot_parts;
+        block_scan2<kWaves>(blocks, parts, &at_block, &at_part, &tot_blocks, &tot_parts, s_w);
+        at_block += before_blocks;
+        at_part += before_parts;
+        if (!tiles) all_parts = tot_parts;
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+            items[0] = make_int4(all_parts, before_blocks + tot_blocks, 0, 0);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            if (p[k] == 1) items[1 + all_parts + at_block++] = make_int4((int)(i0 + k), 0, 1, 0);
+            if (p[k] > 1) {
+                // (there are buffers for every part that the sizes allow)
+                for (int j = 0; j < p[k]; ++j)
+                    items[1 + at_part + j] = make_int4((int)(i0 + k), j, p[k], at_part);
+                at_part += p[k];
+            }
+        }
+    }
     if (blockIdx.x != 0) return;
     float smax = 0.0f;
-    for (int k = threadIdx.x; k < K; k += 256) smax = fmaxf(smax, fabsf(gscale[k]));
+    for (int k = threadIdx.x; k < K; k += kScanBlock) smax = fmaxf(smax, fabsf(gscale[k]));
     for (int off = 32; off > 0; off >>= 1) smax = fmaxf(smax, __shfl_xor(smax, off));
     __syncthreads();
     if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = __float_as_int(smax);   // non-negative: integer order
     __syncthreads();
     if (threadIdx.x == 0) {
         int32_t b = s_w[0];
-        for (int w = 1; w < 4; ++w) b = s_w[w] > b ? s_w[w] : b;
+        for (int w = 1; w < kWaves; ++w) b = s_w[w] > b ? s_w[w] : b;
         bounds[1] = (double)__int_as_float(b);
     }
 }
@@ -640,31 +741,44 @@ __global__ __launch_bounds__(256) void k_adj_runs(int64_t regions, const int32_t
     }
 }
 
-// The adjoint's voxel sums, one work-group per map block (every
-// gridDim.x-th slot below param_blocks): the work-group walks the block's
-// runs of the list (up to kRunBatch runs at a time in LDS, thread t taking
-// entries t, t + 256, ..., kGatherBatch of them per step with each load of
-// a step issued before any is used), recomputes each pixel's point, voxel
-// and residual, and adds s rho' and s rho' (q - v) into its voxel's sums in
-// LDS; then each voxel's gradient is formed from its sums and added to
-// dparams by the one thread that owns the voxel.
-//
-// The sums are 64-bit fixed point (fixed_term).  With n the pixels of the
-// block and s_max = max_i |s_i|, the scale f_p keeps n s_max delta below
-// 2^62 and f_q keeps n s_max delta (v_s / 2 + reach + margin) below 2^62
-// (|q - v| per axis is at most v_s / 2 for the nearest voxel, plus the
-// reach of a frozen association).
-// Largest f in [0, 62] with bound 2^f < 2^62 (bound = m 2^e, 1 <= m < 2:
-// f = 61 - e).
-__device__ inline int fix_scale(double bound) {
+// Largest f with bound 2^f < 2^top (bound = m 2^e, 1 <= m < 2: f = top-1-e),
+// kept where 2^-f and the terms' grid are normal float64 numbers.
+__device__ inline int fix_scale(double bound, int top) {
     if (!(bound > 0.0)) return 62;
-    const int f = 61 - ilogb(bound);
-    return f < 0 ? 0 : (f > 62 ? 62 : f);
+    const int e = ilogb(bound);
+    return e > 900 ? -900 : (e < -900 ? 900 : top - 1 - e);
 }
 
+__device__ inline void store_agent(unsigned long long* p, unsigned long long v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline unsigned long long load_agent(const unsigned long long* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The adjoint's voxel sums, one work-group per map block or part of one (a
+// share of its runs).  The waves take runs in turn; a run lies in one tile of
+// one keyframe, so its pose and the tile's corner are the same for the whole
+// wave.  A lane takes entries l, l + 64, ... of the run (kGatherBatch of them
+// with their loads in flight together), recomputes each pixel's point, voxel
+// and residual from the block's parameters in LDS, and adds s rho' and
+// s rho' (q - v) into its voxel's sums in LDS.  Then each voxel's gradient is
+// formed from its sums and added to dparams by the one thread that owns the
+// voxel; of a block in parts, by the last part to finish, which adds the
+// others' sums from their buffers.
+//
+// The sums are 64-bit fixed point (magic_term), so neither the order of the
+// runs nor the parts change a bit.  With n the pixels of the block and
+// s_max = max_i |s_i|, a term |s rho'| <= s_max delta and |q - v| per axis is
+// at most v_s / 2 + reach + margin (reach: of a frozen association); the
+// scales f_p and f_q keep a term below 2^51 and n terms below 2^62.
+//
+// Bound by VALU issue and the blocks' unevenness: blocks near the cameras hold
+// many times the pixels of others, and one work-group for each ran long after
+// the rest had finished: at
+// 640x480 10 keyframes 79 -> 49 us, 30 keyframes 212 -> 100 us (kernel trace).
 template <bool FREEZE>
-__global__ __launch_bounds__(kAdjBlock) void k_backward_gather(MapView M, AdjArgs a, int32_t K,
-                                                               const float* __restrict__ depth,
+__global__ __launch_bounds__(kAdjBlock) void k_backward_gather(MapView M, AdjArgs a, int32_t ntiles, int32_t tiles_x,
                                                                const double* __restrict__ poses,
                                                                const float4* __restrict__ params,
                                                                const float* __restrict__ gscale,
@@ -675,181 +789,150 @@ __global__ __launch_bounds__(kAdjBlock) void k_backward_gather(MapView M, AdjArg
                                                                const int32_t* __restrict__ run_count,
                                                                const int32_t* __restrict__ run_off,
                                                                const double* __restrict__ bounds,
+                                                               const int4* __restrict__ items,
+                                                               int32_t* __restrict__ done,
+                                                               unsigned long long* __restrict__ buffers,
                                                                float* __restrict__ dparams) {
     __shared__ unsigned long long sP[kBlockVoxels];
     __shared__ unsigned long long sQ[3][kBlockVoxels];
-    __shared__ double s_pose[kPoseLds][12];
-    __shared__ float s_s[kPoseLds];
-    __shared__ int32_t s_rstart[kRunBatch];
-    __shared__ int32_t s_rpre[kRunBatch + 1];
-    __shared__ int32_t s_w[8];
-    const bool lds_pose = K <= kPoseLds;
-    if (lds_pose) {
-        for (int k = threadIdx.x; k < K * 12; k += kAdjBlock) s_pose[k / 12][k % 12] = poses[k];
-        for (int k = threadIdx.x; k < K; k += kAdjBlock) s_s[k] = gscale[k];
+    __shared__ float4 s_par[kBlockVoxels];   // in the map's (Morton) order
+    __shared__ int s_last;
+    int4 item = make_int4((int)blockIdx.x, 0, 1, 0);
+    if (items) {
+        const int4 all = items[0];
+        if ((int)blockIdx.x >= all.x + all.y) return;
+        item = items[1 + blockIdx.x];
+    }
+    const int64_t slot = item.x;
+    const int32_t n = pix_count[slot];
+    if (n == 0) return;
+    const int32_t nruns = run_count[slot], roff = run_off[slot];
+    const int32_t r0 = (int32_t)((int64_t)nruns * item.y / item.z), r1 = (int32_t)((int64_t)nruns * (item.y + 1) / item.z);
+    for (int c = threadIdx.x; c < kBlockVoxels; c += kAdjBlock) {
+        sP[c] = 0ull;
+        sQ[0][c] = sQ[1][c] = sQ[2][c] = 0ull;
+        s_par[c] = params[slot * kBlockVoxels + c];
     }
     const double rmax =
         FREEZE ? __longlong_as_double((long long)reinterpret_cast<const unsigned long long*>(bounds)[0]) : 0.0;
-    const double smax = bounds[1];
     const double margin = 1e-6 * (1.0 + fabs(a.vs) * 1e3);
-    const uint32_t N = (uint32_t)a.W * (uint32_t)a.H;
-    const double invN = 1.0 / (double)N, invW = 1.0 / (double)a.W;
-    int64_t slot = blockIdx.x;
-    int32_t n = slot < a.param_blocks ? pix_count[slot] : 0;
+    const double term_p = bounds[1] * (double)a.delta, term_q = term_p * (0.5 * a.vs + rmax + margin);
+    const int fp = min(fix_scale(term_p, 51), fix_scale(term_p * (double)n, 62));
+    const int fq = min(fix_scale(term_q, 51), fix_scale(term_q * (double)n, 62));
+    const double mp = magic_of(fp), mq = magic_of(fq);
+    const unsigned long long np = 0ull - double_bits(mp), nq = 0ull - double_bits(mq);
     __syncthreads();
-
-    for (; slot < a.param_blocks; slot += gridDim.x, n = slot < a.param_blocks ? pix_count[slot] : 0) {
-        if (n == 0) continue;
-        const int32_t nruns = run_count[slot], roff = run_off[slot];
-        for (int c = threadIdx.x; c < kBlockVoxels; c += kAdjBlock) {
-            sP[c] = 0ull;
-            sQ[0][c] = sQ[1][c] = sQ[2][c] = 0ull;
+    const int lane = threadIdx.x & 63;
+    for (int r = r0 + (int)(threadIdx.x >> 6); r < r1; r += kAdjBlock / 64) {
+        // uniform over the wave
+        const int2 rn = runs[roff + r];
+        const int start = __builtin_amdgcn_readfirstlane(rn.x), count = __builtin_amdgcn_readfirstlane(rn.y);
+        const int region = start / kTilePx;
+        const int kf = region / ntiles, tile = region - kf * ntiles;
+        const int ty = tile / tiles_x, tx = tile - ty * tiles_x;
+        double R[9], t[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) R[3 * i + c] = poses[12 * kf + 4 * i + c];
+            t[i] = poses[12 * kf + 4 * i + 3];
         }
-        const double base_p = (double)n * smax * (double)a.delta;
-        const int fp = fix_scale(base_p), fq = fix_scale(base_p * (0.5 * a.vs + rmax + margin));
-        const float wsp = ldexpf(1.0f, fp), whp = ldexpf(1.0f, fp - 32);
-        const float wsq = ldexpf(1.0f, fq), whq = ldexpf(1.0f, fq - 32);
-        for (int r0 = 0; r0 < nruns; r0 += kRunBatch) {
-            // ---- up to kRunBatch runs: starts and prefix counts in LDS
-            const int nr = nruns - r0 < kRunBatch ? nruns - r0 : kRunBatch;
-            const int2 run = threadIdx.x < nr ? runs[roff + r0 + threadIdx.x] : make_int2(0, 0);
-            int32_t ex, unused, total, tot2;
-            block_scan2(run.y, 0, &ex, &unused, &total, &tot2, s_w);   // its barriers order the clears above
-            s_rstart[threadIdx.x] = run.x;
-            s_rpre[threadIdx.x] = ex;
-            if (threadIdx.x == 0) s_rpre[kRunBatch] = total;
-            __syncthreads();
-            int rc = 0;   // this thread's run (its entries only grow)
-            for (int j0 = threadIdx.x; j0 < total; j0 += kAdjBlock * kGatherBatch) {
-                uint2 le[kGatherBatch];
-                bool live[kGatherBatch];
+        const float s = gscale[kf];
+        for (int j0 = lane; j0 - lane < count; j0 += 64 * kGatherBatch) {
+            uint2 le[kGatherBatch];
+            bool live[kGatherBatch];
+            int m[kGatherBatch][3];
 #pragma unroll
-                for (int b = 0; b < kGatherBatch; ++b) {
-                    const int j = j0 + b * kAdjBlock;
-                    live[b] = j < total;
-                    le[b] = make_uint2(0u, 0u);
-                    if (!live[b]) continue;
-                    while (rc + 1 < nr && j >= s_rpre[rc + 1]) ++rc;
-                    le[b] = list[s_rstart[rc] + (j - s_rpre[rc])];
-                }
-                int m[kGatherBatch][3];
-                uint32_t kk[kGatherBatch];
-                int uu[kGatherBatch], vv[kGatherBatch];
+            for (int b = 0; b < kGatherBatch; ++b) {
+                live[b] = j0 + 64 * b < count;
+                le[b] = live[b] ? list[start + j0 + 64 * b] : make_uint2(0u, 0u);
+            }
 #pragma unroll
-                for (int b = 0; b < kGatherBatch; ++b) {
-                    if (!live[b]) continue;
-                    // keyframe, row and column of the pixel id (the float64
-                    // quotients are within 1 of the integer ones)
-                    const uint32_t p = le[b].x;
-                    int32_t kf = (int32_t)((double)p * invN);
-                    int32_t i = (int32_t)(p - (uint32_t)kf * N);
-                    if (i < 0) {
-                        --kf;
-                        i += (int32_t)N;
-                    } else if (i >= (int32_t)N) {
-                        ++kf;
-                        i -= (int32_t)N;
-                    }
-                    int32_t v = (int32_t)((double)i * invW);
-                    int32_t u = i - v * a.W;
-                    if (u < 0) {
-                        --v;
-                        u += a.W;
-                    } else if (u >= a.W) {
-                        ++v;
-                        u -= a.W;
-                    }
-                    kk[b] = (uint32_t)kf;
-                    uu[b] = u;
-                    vv[b] = v;
-                    if (FREEZE) {
-                        const int32_t* as = assoc + (size_t)p * 3;
-                        m[b][0] = as[0];
-                        m[b][1] = as[1];
-                        m[b][2] = as[2];
-                    }
-                }
-                float4 pr[kGatherBatch];
-                float qf[kGatherBatch][3], dq[kGatherBatch][3];
-                float sv[kGatherBatch];
-#pragma unroll
-                for (int b = 0; b < kGatherBatch; ++b) {
-                    if (!live[b]) continue;
-                    const uint32_t kf = kk[b];
-                    double R[9], t[3];
-                    if (lds_pose) {
-#pragma unroll
-                        for (int r = 0; r < 3; ++r) {
-#pragma unroll
-                            for (int c = 0; c < 3; ++c) R[3 * r + c] = s_pose[kf][4 * r + c];
-                            t[r] = s_pose[kf][4 * r + 3];
-                        }
-                        sv[b] = s_s[kf];
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < 3; ++r) {
-#pragma unroll
-                            for (int c = 0; c < 3; ++c) R[3 * r + c] = poses[12 * kf + 4 * r + c];
-                            t[r] = poses[12 * kf + 4 * r + 3];
-                        }
-                        sv[b] = gscale[kf];
-                    }
-                    double q[3];
-                    pixel_point(a, R, t, __uint_as_float(le[b].y), uu[b], vv[b], q);
-                    if (!FREEZE) nearest_voxel(a, q, m[b]);
-#pragma unroll
-                    for (int r = 0; r < 3; ++r) {
-                        qf[b][r] = (float)q[r];
-                        dq[b][r] = (float)(q[r] - a.vs * (double)m[b][r]);
-                    }
-                    pr[b] = params[slot * kBlockVoxels + morton9(m[b][0] & 7, m[b][1] & 7, m[b][2] & 7)];
-                }
-#pragma unroll
-                for (int b = 0; b < kGatherBatch; ++b) {
-                    if (!live[b]) continue;
-                    const float4 pv = pr[b];
-                    const float n2 = pv.y * pv.y + pv.z * pv.z + pv.w * pv.w;
-                    if (!(n2 > 0.0f)) continue;   // not taken: the pixel pass checked it
-                    PixelTerm P;
-                    P.inv_ng = 1.0f / sqrtf(n2);
-                    P.psi = pv.x;
-                    P.gh[0] = pv.y * P.inv_ng;
-                    P.gh[1] = pv.z * P.inv_ng;
-                    P.gh[2] = pv.w * P.inv_ng;
-#pragma unroll
-                    for (int r = 0; r < 3; ++r) {
-                        P.q[r] = qf[b][r];
-                        P.dq[r] = dq[b][r];
-                    }
-                    const ResidualTerms rt = residual_terms(P, a.delta, sv[b]);
-                    const int c = (m[b][0] & 7) | ((m[b][1] & 7) << 3) | ((m[b][2] & 7) << 6);
-                    atomicAdd(&sP[c], fixed_term(wsp, whp, rt.rp));
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) atomicAdd(&sQ[k][c], fixed_term(wsq, whq, rt.rp * P.dq[k]));
+            for (int b = 0; b < kGatherBatch; ++b) {
+                const int u = tx * kAdjTile + (int)(le[b].x % kAdjTile), v = ty * kAdjTile + (int)(le[b].x / kAdjTile);
+                if (FREEZE && live[b]) {
+                    const int32_t* as = assoc + ((size_t)kf * a.W * a.H + (size_t)v * a.W + u) * 3;
+                    m[b][0] = as[0];
+                    m[b][1] = as[1];
+                    m[b][2] = as[2];
                 }
             }
-            __syncthreads();   // the run table is rewritten by the next batch
+#pragma unroll
+            for (int b = 0; b < kGatherBatch; ++b) {
+                if (!live[b]) continue;
+                const int u = tx * kAdjTile + (int)(le[b].x % kAdjTile), v = ty * kAdjTile + (int)(le[b].x / kAdjTile);
+                double q[3];
+                pixel_point(a, R, t, __uint_as_float(le[b].y), u, v, q);
+                if (!FREEZE) nearest_voxel(a, q, m[b]);
+                PixelTerm P;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) P.dq[k] = (float)(q[k] - a.vs * (double)m[b][k]);
+                const float4 pv = s_par[morton9(m[b][0] & 7, m[b][1] & 7, m[b][2] & 7)];
+                const float n2 = pv.y * pv.y + pv.z * pv.z + pv.w * pv.w;
+                if (!(n2 > 0.0f)) continue;   // not taken: the pixel pass checked it
+                P.inv_ng = 1.0f / sqrtf(n2);
+                P.psi = pv.x;
+                P.gh[0] = pv.y * P.inv_ng;
+                P.gh[1] = pv.z * P.inv_ng;
+                P.gh[2] = pv.w * P.inv_ng;
+                P.q[0] = P.q[1] = P.q[2] = 0.0f;   // (the pose rows are not used here)
+                float rp = residual_terms(P, a.delta, s).rp;
+                rp = rp == rp ? rp : 0.0f;   // a NaN upstream gradient adds nothing
+                const int c = (m[b][0] & 7) | ((m[b][1] & 7) << 3) | ((m[b][2] & 7) << 6);
+                const double w = (double)rp;
+                atomicAdd(&sP[c], magic_term(w + mp, np));
+#pragma unroll
+                for (int k = 0; k < 3; ++k) atomicAdd(&sQ[k][c], magic_term(fma(w, (double)P.dq[k], mq), nq));
+            }
         }
-        // ---- each voxel's gradient from its sums, added once by its owner
-        const double ip = ldexp(1.0, -fp), iq = ldexp(1.0, -fq);
+    }
+    __syncthreads();
+    if (item.z > 1) {
+        // device-scope stores that have completed before the ticket,
+        // device-scope loads after it
+        unsigned long long* mine = buffers + (size_t)(item.w + item.y) * 4 * kBlockVoxels;
         for (int c = threadIdx.x; c < kBlockVoxels; c += kAdjBlock) {
-            const unsigned long long p0 = sP[c], q0 = sQ[0][c], q1 = sQ[1][c], q2 = sQ[2][c];
-            if ((p0 | q0 | q1 | q2) == 0ull) continue;
-            const int64_t vi = slot * kBlockVoxels + morton9(c & 7, (c >> 3) & 7, c >> 6);
-            const float4 p = params[vi];
-            const float inv_ng = 1.0f / sqrtf(p.y * p.y + p.z * p.z + p.w * p.w);
-            const float gh[3] = {p.y * inv_ng, p.z * inv_ng, p.w * inv_ng};
-            const float S[3] = {(float)((double)(long long)q0 * iq), (float)((double)(long long)q1 * iq),
-                                (float)((double)(long long)q2 * iq)};
-            const float gS = gh[0] * S[0] + gh[1] * S[1] + gh[2] * S[2];
-            float4 d = reinterpret_cast<float4*>(dparams)[vi];
-            d.x += (float)((double)(long long)p0 * ip);
-            d.y += inv_ng * (S[0] - gh[0] * gS);
-            d.z += inv_ng * (S[1] - gh[1] * gS);
-            d.w += inv_ng * (S[2] - gh[2] * gS);
-            reinterpret_cast<float4*>(dparams)[vi] = d;
+            store_agent(&mine[c], sP[c]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) store_agent(&mine[(1 + k) * kBlockVoxels + c], sQ[k][c]);
         }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // the stores stay above
+        __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
+        if (threadIdx.x == 0)
+            s_last = __hip_atomic_fetch_add(&done[slot], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == item.z - 1;
+        __syncthreads();
+        if (!s_last) return;
+#pragma unroll 1
+        for (int o = 0; o < item.z; ++o) {
+            if (o == item.y) continue;
+            const unsigned long long* other = buffers + (size_t)(item.w + o) * 4 * kBlockVoxels;
+            for (int c = threadIdx.x; c < kBlockVoxels; c += kAdjBlock) {
+                sP[c] += load_agent(&other[c]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) sQ[k][c] += load_agent(&other[(1 + k) * kBlockVoxels + c]);
+            }
+        }
+    }
+    // ---- each voxel's gradient from its sums, added once by its owner
+    const double ip = ldexp(1.0, -fp), iq = ldexp(1.0, -fq);
+    for (int c = threadIdx.x; c < kBlockVoxels; c += kAdjBlock) {
+        const unsigned long long p0 = sP[c], q0 = sQ[0][c], q1 = sQ[1][c], q2 = sQ[2][c];
+        if ((p0 | q0 | q1 | q2) == 0ull) continue;
+        const int mo = morton9(c & 7, (c >> 3) & 7, c >> 6);
+        const int64_t vi = slot * kBlockVoxels + mo;
+        const float4 p = s_par[mo];
+        const float inv_ng = 1.0f / sqrtf(p.y * p.y + p.z * p.z + p.w * p.w);
+        const float gh[3] = {p.y * inv_ng, p.z * inv_ng, p.w * inv_ng};
+        const float S[3] = {(float)((double)(long long)q0 * iq), (float)((double)(long long)q1 * iq),
+                            (float)((double)(long long)q2 * iq)};
+        const float gS = gh[0] * S[0] + gh[1] * S[1] + gh[2] * S[2];
+        float4 d = reinterpret_cast<float4*>(dparams)[vi];
+        d.x += (float)((double)(long long)p0 * ip);
+        d.y += inv_ng * (S[0] - gh[0] * gS);
+        d.z += inv_ng * (S[1] - gh[1] * gS);
+        d.w += inv_ng * (S[2] - gh[2] * gS);
+        reinterpret_cast<float4*>(dparams)[vi] = d;
     }
 }
 
@@ -979,7 +1062,7 @@ size_t gsdf_keyframe_scratch_bytes(const gsdf_camera* cam, int32_t n_keyframes, 
     if (!valid_cam(cam) || n_keyframes <= 0 || n_keyframes > 65535 || param_blocks < 0) return 0;
     const int64_t tiles = adj_tiles(cam->width, cam->height);
     if ((int64_t)n_keyframes * tiles * kTilePx > (int64_t)INT32_MAX) return 0;   // list entries are int32
-    return adj_scratch(n_keyframes, tiles, param_blocks).total;
+    return adj_scratch(n_keyframes, tiles, param_blocks).split_total;
 }
 
 static int keyframe_common(const gsdf_map* map, const float* depth_dev, int32_t K, const gsdf_camera* cam,
@@ -988,8 +1071,9 @@ static int keyframe_common(const gsdf_map* map, const float* depth_dev, int32_t 
     if (!valid_map(map) || !valid_cam(cam) || K <= 0 || K > 65535 || !depth_dev || !T0_dev || !xi_dev ||
         !params_dev || param_blocks < 0 || param_blocks > map->desc.max_blocks || !(huber_delta > 0.0f) || !scratch)
         return GSDF_EINVAL;
-    const size_t need = gsdf_keyframe_scratch_bytes(cam, K, param_blocks);
-    if (need == 0 || scratch_bytes < need) return GSDF_EINVAL;
+    if (gsdf_keyframe_scratch_bytes(cam, K, param_blocks) == 0 ||
+        scratch_bytes < adj_scratch(K, adj_tiles(cam->width, cam->height), param_blocks).total)
+        return GSDF_EINVAL;
     if (!has_gradients(map)) return GSDF_EINVAL;
     return GSDF_OK;
 }
@@ -1009,7 +1093,7 @@ int gsdf_keyframe_loss(const gsdf_map* map, const float* depth_dev, int32_t n_ke
     double* partials = (double*)(base + L.partials);
     double* poses = (double*)(base + L.poses);
     k_adj_setup<<<ceil_div(n_keyframes, 64), 64, 0, s>>>(n_keyframes, T0_dev, xi_dev, poses, 0, nullptr, nullptr,
-                                                        nullptr, nullptr);
+                                                        nullptr, nullptr, nullptr);
     {
         TimedLaunch tl(map->timer, GSDF_K_LOSS, s);
         const dim3 grid(a.groups, n_keyframes);
@@ -1057,13 +1141,21 @@ int gsdf_backward(const gsdf_map* map, const float* depth_dev, int32_t n_keyfram
     const float4* P = reinterpret_cast<const float4*>(params_dev);
     const int64_t nb = param_blocks;
     const int nscan = (int)ceil_div(nb, (int64_t)kScanTile);
-    const int groups = (int)(nb < kBackGroups ? nb : kBackGroups);
+    // room for the gather's pieces: else every block whole
+    const bool split = scratch_bytes >= L.split_total;
+    const int32_t piece = split ? L.piece : 0;
+    int32_t* piece_tiles = (int32_t*)(base + L.tile_sums);
+    int4* items = split ? (int4*)(base + L.items) : nullptr;
+    int32_t* done = split ? (int32_t*)(base + L.done) : nullptr;
+    unsigned long long* buffers = split ? (unsigned long long*)(base + L.buffers) : nullptr;
+    const int64_t groups = split ? nb + L.n_buffers : nb;
+    const int32_t tiles_x = (cam->width + kAdjTile - 1) / kAdjTile;
     const int64_t setup_n = nb > K ? nb : K;
     const dim3 pgrid(a.groups, K);
     {
         TimedLaunch tl(map->timer, GSDF_K_BACKWARD, s);
         k_adj_setup<<<(unsigned)ceil_div(setup_n, (int64_t)256), 256, 0, s>>>(K, T0_dev, xi_dev, poses, nb, pix_count,
-                                                                           run_count, cursor, reach);
+                                                                           run_count, cursor, done, reach);
         if (freeze)
             k_adj_pixels<true><<<pgrid, kAdjBlock, 0, s>>>(M, a, depth_dev, poses, P, grad_loss_dev, assoc_dev, list,
                                                            recs, nrec, pix_count, run_count, reach, partials);
@@ -1071,20 +1163,20 @@ int gsdf_backward(const gsdf_map* map, const float* depth_dev, int32_t n_keyfram
             k_adj_pixels<false><<<pgrid, kAdjBlock, 0, s>>>(M, a, depth_dev, poses, P, grad_loss_dev, nullptr, list,
                                                             recs, nrec, pix_count, run_count, reach, partials);
         if (nb > 0) {
-            if (nscan > 1) k_adj_tile_sums<<<nscan, 256, 0, s>>>(nb, run_count, tiles);
-            k_adj_offsets<<<nscan, 256, 0, s>>>(nb, run_count, nscan > 1 ? tiles : nullptr, run_off, K,
-                                                grad_loss_dev, bounds);
+            if (nscan > 1) k_adj_tile_sums<<<nscan, 256, 0, s>>>(nb, run_count, pix_count, piece, tiles, piece_tiles);
+            k_adj_offsets<<<nscan, kScanBlock, 0, s>>>(nb, run_count, nscan > 1 ? tiles : nullptr, run_off, K,
+                                                grad_loss_dev, bounds, pix_count, piece, piece_tiles, items);
             const int64_t regions = (int64_t)K * ntiles;
             k_adj_runs<<<(unsigned)ceil_div(regions, (int64_t)4), 256, 0, s>>>(regions, nrec, recs, run_off, cursor,
                                                                                runs);
             if (freeze)
-                k_backward_gather<true><<<groups, kAdjBlock, 0, s>>>(M, a, K, depth_dev, poses, P, grad_loss_dev,
-                                                                     assoc_dev, list, runs, pix_count, run_count,
-                                                                     run_off, bounds, dparams_dev);
+                k_backward_gather<true><<<(unsigned)groups, kAdjBlock, 0, s>>>(
+                    M, a, (int32_t)ntiles, tiles_x, poses, P, grad_loss_dev, assoc_dev, list, runs, pix_count,
+                    run_count, run_off, bounds, items, done, buffers, dparams_dev);
             else
-                k_backward_gather<false><<<groups, kAdjBlock, 0, s>>>(M, a, K, depth_dev, poses, P, grad_loss_dev,
-                                                                      nullptr, list, runs, pix_count, run_count,
-                                                                      run_off, bounds, dparams_dev);
+                k_backward_gather<false><<<(unsigned)groups, kAdjBlock, 0, s>>>(
+                    M, a, (int32_t)ntiles, tiles_x, poses, P, grad_loss_dev, nullptr, list, runs, pix_count,
+                    run_count, run_off, bounds, items, done, buffers, dparams_dev);
         }
         k_keyframe_finish<<<K, 256, 0, s>>>(a.groups, xi_dev, partials, loss_dev, dxi_dev, nullptr);
     }
