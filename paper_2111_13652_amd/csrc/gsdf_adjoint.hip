@@ -211,7 +211,7 @@ __device__ inline void lookup_batch(const MapView& M, const AdjArgs& a, const do
         probe[j] = key_in_range(bx, by, bz);
         if (!probe[j]) continue;
         key[j] = pack_key(bx, by, bz);
-        h[j] = mix64(key[j]) & M.mask;
+        h[j] = block_hash(bx, by, bz) & M.mask;
         e[j] = *reinterpret_cast<const uint4*>(&M.hash[h[j]]);
     }
 #pragma unroll
@@ -434,8 +434,10 @@ __device__ inline void block_scan2(int32_t a, int32_t b, int32_t* ex_a, int32_t*
 // points lie outside the cells of their frozen voxels, as the bits of a
 // non-negative float64 (whose integer order is its numeric order); that
 // bounds the offsets q - v of the voxel sums.
+// Registers: 99 (109 frozen) hold four waves to a SIMD; the plain form fits
+// five by spilling two.
 template <bool FREEZE>
-__global__ __launch_bounds__(kAdjBlock) void k_adj_pixels(MapView M, AdjArgs a, const float* __restrict__ depth,
+__global__ __launch_bounds__(kAdjBlock, FREEZE ? 4 : 5) void k_adj_pixels(MapView M, AdjArgs a, const float* __restrict__ depth,
                                                           const double* __restrict__ poses,
                                                           const float4* __restrict__ params,
                                                           const float* __restrict__ gscale,

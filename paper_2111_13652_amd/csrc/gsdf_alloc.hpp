@@ -56,7 +56,7 @@ __device__ inline void allocate_tile(const MapView& M, const float* __restrict__
             pb[2] = bz;
             if (!block_allowed(M, bx, by, bz)) continue;
             const unsigned long long key = pack_key(bx, by, bz);
-            unsigned h = (unsigned)mix64(key) & (kAllocSet - 1);
+            unsigned h = block_hash(bx, by, bz) & (kAllocSet - 1);
             bool placed = false;
             for (int probe = 0; probe < kAllocSet; ++probe) {
                 const unsigned long long old = atomicCAS(&s_keys[h], kEmptyKey, key);

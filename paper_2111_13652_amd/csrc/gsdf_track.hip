@@ -41,8 +41,25 @@ constexpr unsigned kTagPolls = 1u << 20;
 struct TrackLevel {
     const float* depth;
     int W, H;
+    double inv_w;   // 1 / W
     double ifx, ify, cx, cy;
 };
+
+// Row and column of pixel i of a level: the float64 quotient is within 1 of
+// the integer one (an integer division is some 25 instructions).
+__device__ inline void pixel_of(const TrackLevel& L, int i, int* u, int* v) {
+    int row = (int)((double)i * L.inv_w);
+    int col = i - row * L.W;
+    if (col < 0) {
+        --row;
+        col += L.W;
+    } else if (col >= L.W) {
+        ++row;
+        col -= L.W;
+    }
+    *u = col;
+    *v = row;
+}
 
 struct TrackArgs {
     TrackLevel lv[4];
@@ -90,12 +107,11 @@ struct Kahan {
 // first, first + stride, ... below end.
 constexpr int kTrackBatch = 3;
 
-template <int STORAGE>
+template <int STORAGE, int B = kTrackBatch>
 __device__ inline void accumulate(const MapView& M, const TrackLevel& L, const TrackArgs& a,
                                   const double* pose, int first, int stride, int end, const float* Dpre,
                                   float acc[kNE], float cmp[kNE]) {
     constexpr bool kPrecision = STORAGE == GSDF_BF16 || STORAGE == GSDF_FP16;
-    constexpr int B = kTrackBatch;
     Kahan ks[kNE];
 #pragma unroll
     for (int k = 0; k < kNE; ++k) acc[k] = 0.0f;
@@ -141,8 +157,8 @@ __device__ inline void accumulate(const MapView& M, const TrackLevel& L, const T
             live[j] = i < N && depth_ok(D[j], a.zmin, a.zmax);
             if (!live[j]) continue;
             if (kPrecision) ks[29].add(1.0f); else acc[29] += 1.0f;
-            const int v = i / L.W;
-            const int u = i - v * L.W;
+            int u, v;
+            pixel_of(L, i, &u, &v);
             if (!kPrecision) {
                 const double Dd = (double)D[j];
                 const double x0 = Dd * (((double)u - L.cx) * L.ifx);
@@ -150,8 +166,9 @@ __device__ inline void accumulate(const MapView& M, const TrackLevel& L, const T
 #pragma unroll
                 for (int r = 0; r < 3; ++r) {
                     const double q = R[3 * r] * x0 + R[3 * r + 1] * x1 + R[3 * r + 2] * Dd + t[r];
-                    m[j][r] = (int)floor(q * a.inv_vs + 0.5);
-                    qr[j][r] = (float)(q - a.vs * (double)m[j][r]);
+                    const double near = floor(q * a.inv_vs + 0.5);
+                    m[j][r] = (int)near;
+                    qr[j][r] = (float)(q - a.vs * near);
                     qf[j][r] = (float)q;
                 }
             } else {
@@ -172,7 +189,7 @@ __device__ inline void accumulate(const MapView& M, const TrackLevel& L, const T
                 continue;
             }
             key[j] = pack_key(bx, by, bz);
-            h[j] = mix64(key[j]) & M.mask;
+            h[j] = block_hash(bx, by, bz) & M.mask;
             e[j] = *reinterpret_cast<const uint4*>(&M.hash[h[j]]);
         }
         // ---- stage 3: resolve the probe, then weight and record together
@@ -324,8 +341,8 @@ __device__ inline void accumulate_trilinear(const MapView& M, const TrackLevel& 
             live[j] = i < N && depth_ok(D[j], a.zmin, a.zmax);
             if (!live[j]) continue;
             if (kPrecision) ks[29].add(1.0f); else acc[29] += 1.0f;
-            const int v = i / L.W;
-            const int u = i - v * L.W;
+            int u, v;
+            pixel_of(L, i, &u, &v);
             const double Dd = (double)D[j];
             const double x0 = Dd * (((double)u - L.cx) * L.ifx);
             const double x1 = Dd * (((double)v - L.cy) * L.ify);
@@ -1191,9 +1208,17 @@ __global__ __launch_bounds__(kTrackBlock) void k_normal_equations(MapView M, Tra
 // left update of k_track_frame.  The keyframes' pixel work shares one
 // launch, so a refinement step pays two launches instead of two per
 // keyframe.
+// Bound by the waves in flight: the float32 form at three pixels a batch
+// holds 130 registers a thread, one work-group a CU; at two it holds 110 and
+// two work-groups share a CU (the step at 30 keyframes of 640x480: 116 us
+// before, 75 with them).  The compensated sums of the 16-bit form need 170
+// and stay at three (at 128 registers they spill).
 template <int STORAGE>
-__global__ __launch_bounds__(kTrackBlock) void k_gn_partials(MapView M, TrackArgs a, const double* poses,
-                                                            double* partials) {
+constexpr int kGnBatch = STORAGE == GSDF_FP32 ? 2 : kTrackBatch;
+
+template <int STORAGE>
+__global__ __launch_bounds__(kTrackBlock, STORAGE == GSDF_FP32 ? 4 : 2) void k_gn_partials(
+    MapView M, TrackArgs a, const double* poses, double* partials) {
     __shared__ ReduceLds red;
     constexpr bool COMP = STORAGE == GSDF_BF16 || STORAGE == GSDF_FP16;
     const int k = blockIdx.y;
@@ -1205,8 +1230,8 @@ __global__ __launch_bounds__(kTrackBlock) void k_gn_partials(MapView M, TrackArg
     L.depth += (size_t)k * npx;
     float acc[kNE], cmp[kNE];
     if (pose_finite(P)) {
-        accumulate<STORAGE>(M, L, a, P, blockIdx.x * kTrackBlock + threadIdx.x, gridDim.x * kTrackBlock, npx,
-                            nullptr, acc, cmp);
+        accumulate<STORAGE, kGnBatch<STORAGE>>(M, L, a, P, blockIdx.x * kTrackBlock + threadIdx.x,
+                                      gridDim.x * kTrackBlock, npx, nullptr, acc, cmp);
     } else {
         // the solve leaves this keyframe as it is and reports it
 #pragma unroll
@@ -1353,8 +1378,8 @@ constexpr int kMaxGnKeyframes = 65535;
 // Work-groups per keyframe of the batched Gauss-Newton step: about 8
 // pixels a thread, so the work-group's fixed costs (its partial's LDS sum
 // and store) are shared by more pixels.  Measured at 30 keyframes of
-// 640x480: 190 us at 2 pixels a thread, 160 at 4, 138 at 8, 132 at 16
-// (which leaves most CUs idle below about 8 keyframes).
+// 640x480 with one work-group on a CU: 190 us at 2 pixels a thread, 160 at 4,
+// 138 at 8, 132 at 16 (which leaves most CUs idle below about 8 keyframes).
 inline int gn_groups(int npx) {
     const int g = ceil_div(npx, kTrackBlock * 8);
     return g < 1 ? 1 : (g > kMaxGroups ? kMaxGroups : g);
@@ -1417,6 +1442,7 @@ inline void fill_levels(const gsdf_camera& cam, const float* depth, const Scratc
     a->lv[0].depth = depth;
     a->lv[0].W = cam.width;
     a->lv[0].H = cam.height;
+    a->lv[0].inv_w = 1.0 / cam.width;
     a->lv[0].ifx = 1.0 / fx;
     a->lv[0].ify = 1.0 / fy;
     a->lv[0].cx = cx;
@@ -1429,6 +1455,7 @@ inline void fill_levels(const gsdf_camera& cam, const float* depth, const Scratc
         a->lv[l].depth = l < levels ? (const float*)(base + sl.level[l]) : nullptr;
         a->lv[l].W = a->lv[l - 1].W / 2;
         a->lv[l].H = a->lv[l - 1].H / 2;
+        a->lv[l].inv_w = a->lv[l].W > 0 ? 1.0 / a->lv[l].W : 0.0;
         a->lv[l].ifx = 1.0 / fx;
         a->lv[l].ify = 1.0 / fy;
         a->lv[l].cx = cx;
