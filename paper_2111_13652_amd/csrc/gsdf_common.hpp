@@ -85,9 +85,9 @@ struct alignas(16) HashEntry {
 
 // Voxel index inside a block: Morton order of (lx, ly, lz), so every 2x2x2
 // sub-cube (8 voxels) is contiguous.
-__host__ __device__ inline int spread3(int x) {  // bits b0 b1 b2 -> positions 0, 3, 6
-    return (x & 1) | ((x & 2) << 2) | ((x & 4) << 4);
-}
+// Bits b0 b1 b2 of x -> positions 0, 3, 6: a byte of a table of eight (three
+// instructions; masks and shifts take seven).
+__host__ __device__ inline int spread3(int x) { return (int)(0x4948414009080100ull >> ((x << 3) & 56)) & 0xff; }
 __host__ __device__ inline int morton9(int lx, int ly, int lz) {
     return spread3(lx) | (spread3(ly) << 1) | (spread3(lz) << 2);
 }

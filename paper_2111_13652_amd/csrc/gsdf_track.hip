@@ -45,20 +45,20 @@ struct TrackLevel {
     double ifx, ify, cx, cy;
 };
 
-// Row and column of pixel i of a level: the float64 quotient is within 1 of
-// the integer one (an integer division is some 25 instructions).
+// Row and column of pixel i of a level.  (i + 1/2) / W lies 1/(2 W) or more
+// from an integer and the float64 product within 2^-52 H of it, so the row
+// is exact for every i that an int holds (an integer division takes some 25
+// instructions, this 5).
 __device__ inline void pixel_of(const TrackLevel& L, int i, int* u, int* v) {
-    int row = (int)((double)i * L.inv_w);
-    int col = i - row * L.W;
-    if (col < 0) {
-        --row;
-        col += L.W;
-    } else if (col >= L.W) {
-        ++row;
-        col -= L.W;
-    }
-    *u = col;
-    *v = row;
+    *v = (int)(((double)i + 0.5) * L.inv_w);
+    *u = i - *v * L.W;
+}
+
+// a += x y, in a's own register.  (Where an update stands under a condition
+// the compiler gives the sum a register of its own and copies it back: 16
+// copies a pixel.)
+__device__ inline void add_product(float& a, float x, float y) {
+    asm("v_fmac_f32_e32 %0, %1, %2" : "+v"(a) : "v"(x), "v"(y));
 }
 
 struct TrackArgs {
@@ -268,13 +268,13 @@ __device__ inline void accumulate(const MapView& M, const TrackLevel& L, const T
                 const float wj = w * J[p];
 #pragma unroll
                 for (int q2 = p; q2 < 6; ++q2) {
-                    if (kPrecision) ks[k].add(wj * J[q2]); else acc[k] += wj * J[q2];
+                    if (kPrecision) ks[k].add(wj * J[q2]); else add_product(acc[k], wj, J[q2]);
                     ++k;
                 }
             }
 #pragma unroll
             for (int p = 0; p < 6; ++p) {
-                if (kPrecision) ks[21 + p].add(w * J[p] * r); else acc[21 + p] += w * J[p] * r;
+                if (kPrecision) ks[21 + p].add(w * J[p] * r); else add_product(acc[21 + p], w * J[p], r);
             }
             if (kPrecision) {
                 ks[27].add(en);
@@ -427,13 +427,13 @@ __device__ inline void accumulate_trilinear(const MapView& M, const TrackLevel& 
                 const float wj = w * J[p];
 #pragma unroll
                 for (int q2 = p; q2 < 6; ++q2) {
-                    if (kPrecision) ks[k].add(wj * J[q2]); else acc[k] += wj * J[q2];
+                    if (kPrecision) ks[k].add(wj * J[q2]); else add_product(acc[k], wj, J[q2]);
                     ++k;
                 }
             }
 #pragma unroll
             for (int p = 0; p < 6; ++p) {
-                if (kPrecision) ks[21 + p].add(w * J[p] * r); else acc[21 + p] += w * J[p] * r;
+                if (kPrecision) ks[21 + p].add(w * J[p] * r); else add_product(acc[21 + p], w * J[p], r);
             }
             if (kPrecision) {
                 ks[27].add(en);
@@ -456,33 +456,52 @@ __device__ inline void accumulate_trilinear(const MapView& M, const TrackLevel& 
 }
 
 // Work-group sum: every thread writes its kNE sums to LDS (one transpose),
-// then 8 threads per entry add kRedChunk values each with independent LDS
-// reads, and the first kNE threads combine the 8 parts and store the
-// work-group partial with device-scope stores.  (Cross-lane shuffles of
-// doubles would chain ~180 dependent LDS permutes per wave.)  Each entry's
-// row is 8 chunks of kRedChunk values, kRedPad floats apart, so that the 8
-// lanes of one 16-byte read pass (the 8 chunks of an entry) fall in
-// different banks.  The plain path adds each chunk (one wave's values) four
-// at a time in float32, then those sums and the 8 chunk sums by pairwise
-// trees in float64: the serial float64 chain it replaces (64 conversions
-// and adds per thread, then 8 more adds) was the longest dependent sequence
-// of the sum (measured: 3.5 us less per tracking launch at 640x480).  A
+// then 16 threads per entry add kRedChunk values each with independent LDS
+// reads, and the 16 sums are added across the lanes.  Each entry's row is 16
+// chunks of kRedChunk values, kRedPad floats apart, so that the 16 lanes of
+// one 16-byte read pass (the chunks of an entry) fall in different banks.
+// The plain path adds each chunk four values at a time in float32, then
+// those sums and the 16 chunk sums by pairwise trees in float64 (a serial
+// float64 chain costs 3.5 us more per tracking launch at 640x480).  A
 // float32 tree over a whole chunk is 0.6 us faster still but loses what
 // float64 keeps: where a thread holds a single pixel its sums are exact
 // products, and on an ill-conditioned system (a sphere, whose rotations
 // about its centre leave the residuals unchanged) the tracked centre moved
 // 40 times further from the float64 oracle's.  The precision form
-// (COMP) uses compensated float32 at every stage.  The storing threads are
-// lanes of wave 0, so thread 0 (which takes the arrival ticket, where there
-// is one) waits for their completion before signalling.
-constexpr int kRedChunk = kTrackBlock / 8;
+// (COMP) uses compensated float32 at every stage: 8 threads per entry, two
+// chunks each, then the first kNE threads add the 8 parts.
+//
+// Bound by issue and by LDS round trips (a wave alone on its SIMD issues
+// every 8 cycles): 8 threads per entry, their parts through LDS and a second
+// barrier to the 30 threads that add them made an iteration of tracking
+// 0.4 us longer, and again where partials or leaf sums are added.
+constexpr int kRedChunk = kTrackBlock / 16;
 constexpr int kRedPad = kRedChunk + 4;
 struct ReduceLds {
-    float v[kNE][8 * kRedPad];
-    double part[kNE][8];
+    float v[kNE][16 * kRedPad];
+    double part[3][kNE][8];   // COMP: of store_partial, and of two sums after it: no barrier between them
     double tot[kNE];
+    int fail;                 // a wait of total_leaves ended without its tag
 };
 __device__ inline int red_slot(int t) { return (t / kRedChunk) * kRedPad + t % kRedChunk; }
+
+// Sum over aligned groups of N = 8 or 16 lanes (every lane gets it), by
+// moves inside a row of lanes.
+template <int CTRL>
+__device__ inline double lane_move(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+template <int N>
+__device__ inline double lane_sum(double v) {
+    v += lane_move<0xB1>(v);                 // quad_perm: lane ^ 1
+    v += lane_move<0x4E>(v);                 // quad_perm: lane ^ 2
+    v += lane_move<0x141>(v);                // row_half_mirror: the other four of 8
+    if (N == 16) v += lane_move<0x140>(v);   // row_mirror: the other eight of 16
+    return v;
+}
 
 // Partials and leaf sums of the tracking kernel carry the iteration they
 // belong to: the low 16 bits of each float64 word (a relative change below
@@ -497,7 +516,19 @@ __device__ inline unsigned long long tag_word(double v, unsigned long long tag) 
 __device__ inline double untag_word(unsigned long long w) { return __longlong_as_double((long long)(w & ~kTagMask)); }
 
 // A tagged partial (tag != 0) is stored at work-group scope when `local`
-// (its reader runs on the same XCD), else at device scope.
+// (its reader runs on the same XCD), else at device scope.  An untagged one
+// is complete when the call returns.
+__device__ inline void store_entry(double* partial, int k, double s, unsigned long long tag, bool local) {
+    if (tag && local)
+        __hip_atomic_store(reinterpret_cast<unsigned long long*>(&partial[k]), tag_word(s, tag), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+    else if (tag)
+        __hip_atomic_store(reinterpret_cast<unsigned long long*>(&partial[k]), tag_word(s, tag), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    else
+        __hip_atomic_store(&partial[k], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 template <bool COMP>
 __device__ inline void store_partial(const float acc[kNE], const float cmp[kNE], double* partial,
                                      ReduceLds& r, unsigned long long tag = 0, bool local = false) {
@@ -505,23 +536,31 @@ __device__ inline void store_partial(const float acc[kNE], const float cmp[kNE],
 #pragma unroll
     for (int k = 0; k < kNE; ++k) r.v[k][slot] = COMP ? acc[k] - cmp[k] : acc[k];
     __syncthreads();
-    if (threadIdx.x < kNE * 8) {
-        const int k = threadIdx.x >> 3, p = threadIdx.x & 7;
-        const float4* src = reinterpret_cast<const float4*>(&r.v[k][p * kRedPad]);
-        float4 q[kRedChunk / 4];
-#pragma unroll
-        for (int j = 0; j < kRedChunk / 4; ++j) q[j] = src[j];
+    constexpr int kLanes = COMP ? 8 : 16;
+    if (threadIdx.x < kNE * kLanes) {
+        const int k = threadIdx.x / kLanes, p = threadIdx.x % kLanes;
         if (COMP) {
             Kahan ks;
 #pragma unroll
-            for (int j = 0; j < kRedChunk / 4; ++j) {
-                ks.add(q[j].x);
-                ks.add(q[j].y);
-                ks.add(q[j].z);
-                ks.add(q[j].w);
+            for (int h = 0; h < 2; ++h) {
+                const float4* src = reinterpret_cast<const float4*>(&r.v[k][(2 * p + h) * kRedPad]);
+                float4 q[kRedChunk / 4];
+#pragma unroll
+                for (int j = 0; j < kRedChunk / 4; ++j) q[j] = src[j];
+#pragma unroll
+                for (int j = 0; j < kRedChunk / 4; ++j) {
+                    ks.add(q[j].x);
+                    ks.add(q[j].y);
+                    ks.add(q[j].z);
+                    ks.add(q[j].w);
+                }
             }
-            r.part[k][p] = (double)ks.value();
+            r.part[0][k][p] = (double)ks.value();
         } else {
+            const float4* src = reinterpret_cast<const float4*>(&r.v[k][p * kRedPad]);
+            float4 q[kRedChunk / 4];
+#pragma unroll
+            for (int j = 0; j < kRedChunk / 4; ++j) q[j] = src[j];
             double t[kRedChunk / 4];
 #pragma unroll
             for (int j = 0; j < kRedChunk / 4; ++j) t[j] = (double)((q[j].x + q[j].y) + (q[j].z + q[j].w));
@@ -530,38 +569,23 @@ __device__ inline void store_partial(const float acc[kNE], const float cmp[kNE],
 #pragma unroll
                 for (int j = 0; j < w; ++j) t[j] = t[j] + t[j + w];
             }
-            r.part[k][p] = t[0];
+            const double s = lane_sum<16>(t[0]);
+            if (p == 0) store_entry(partial, k, s, tag, local);
         }
     }
-    __syncthreads();
-    if (threadIdx.x < kNE) {
-        double s = 0.0;
-        if (COMP) {
+    if (COMP) {
+        __syncthreads();
+        if (threadIdx.x < kNE) {
             Kahan ks;
 #pragma unroll
-            for (int p = 0; p < 8; ++p) ks.add((float)r.part[threadIdx.x][p]);
-            s = (double)ks.value();
-        } else {
-            double t[8];
-#pragma unroll
-            for (int p = 0; p < 8; ++p) t[p] = r.part[threadIdx.x][p];
-#pragma unroll
-            for (int w = 4; w >= 1; w /= 2) {
-#pragma unroll
-                for (int j = 0; j < w; ++j) t[j] = t[j] + t[j + w];
-            }
-            s = t[0];
+            for (int p = 0; p < 8; ++p) ks.add((float)r.part[0][threadIdx.x][p]);
+            store_entry(partial, threadIdx.x, (double)ks.value(), tag, local);
         }
-        if (tag && local)
-            __hip_atomic_store(reinterpret_cast<unsigned long long*>(&partial[threadIdx.x]), tag_word(s, tag),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        else if (tag)
-            __hip_atomic_store(reinterpret_cast<unsigned long long*>(&partial[threadIdx.x]), tag_word(s, tag),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else
-            __hip_atomic_store(&partial[threadIdx.x], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __syncthreads();
+    if (!tag) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    }
 }
 
 // Sum of `groups` partials (device-scope loads, issued after the signal
@@ -602,45 +626,24 @@ __device__ inline void total_partials(const double* partials, int groups, double
                                                __HIP_MEMORY_SCOPE_AGENT);
             if (COMP) ks.add((float)x); else s += x;
         }
-        r.part[k][p] = COMP ? (double)ks.value() : s;
+        r.part[1][k][p] = COMP ? (double)ks.value() : s;
     }
     __syncthreads();
     if (threadIdx.x < kNE) {
         const int k = threadIdx.x;
         if (COMP) {
             Kahan ks;
-            for (int p = 0; p < 8; ++p) ks.add((float)r.part[k][p]);
+            for (int p = 0; p < 8; ++p) ks.add((float)r.part[1][k][p]);
             r.tot[k] = (double)ks.value();
         } else {
             double t = 0.0;
-            for (int p = 0; p < 8; ++p) t += r.part[k][p];
+            for (int p = 0; p < 8; ++p) t += r.part[1][k][p];
             r.tot[k] = t;
         }
     }
     __syncthreads();
     if (threadIdx.x == 0)
         for (int k = 0; k < kNE; ++k) ne[k] = r.tot[k];
-}
-
-// The damped 6x6 solve and the left pose update, by one wave.
-//
-// Lane i < 6 holds row i of [H + mu I | -b] (mu = damping tr(H)/6).
-// Gaussian elimination without pivoting: H + mu I is symmetric positive
-// definite, so every pivot is positive and this is its LDL^T factorisation
-// (the same solution as a Cholesky solve, with no square roots).  The pivot
-// row is broadcast with readlane, each lane below it eliminates its own
-// entry, and back substitution broadcasts each unknown as it is found.  Then
-// lane k < 12 forms entry k = 4 i + j of exp(x^) T from row i of R and V
-// (the closed forms of se3_exp) and column j of T.  ne is the float64 sum
-// (21 upper entries of H row by row, then b) in LDS; pose is the 3x4 pose in
-// LDS, replaced in place.  Every lane returns the same flag: false when a
-// pivot is not positive, with the pose unchanged.
-
-__device__ inline double bcast_lane(double v, int lane) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __hiloint2double(hi, lo);
 }
 
 // 1/p to within an ulp: hardware reciprocal and one Newton step.
@@ -650,47 +653,73 @@ __device__ inline double recip(double p) {
     return fma(r, e, r);
 }
 
-__device__ inline int upper_index(int i, int j) { return i * 6 - (i * (i - 1)) / 2 + (j - i); }  // i <= j
+__device__ __host__ constexpr int upper_index(int i, int j) { return i * 6 - (i * (i - 1)) / 2 + (j - i); }  // i <= j
 
+// (exp(phi^) - I) v by the closed form's coefficients: a (phi x v) +
+// b (phi (phi . v) - |phi|^2 v).
+__device__ inline void twist_apply(const double p[3], double th2, double a, double b, const double v[3],
+                                   double out[3]) {
+    const double d = fma(p[0], v[0], fma(p[1], v[1], p[2] * v[2]));
+    const double c[3] = {fma(p[1], v[2], -(p[2] * v[1])), fma(p[2], v[0], -(p[0] * v[2])),
+                         fma(p[0], v[1], -(p[1] * v[0]))};
+#pragma unroll
+    for (int r = 0; r < 3; ++r) out[r] = fma(a, c[r], b * fma(p[r], d, -(th2 * v[r])));
+}
+
+// The damped 6x6 solve and the left pose update, by one wave: LDL^T of
+// H + mu I (mu = damping tr(H)/6; symmetric positive definite, so every pivot
+// is positive, with no pivoting and no square roots), then exp(x^) T.  ne is
+// the float64 sum (21 upper entries of H row by row, then b) in LDS; pose is
+// the 3x4 pose in LDS, replaced in place.  Every lane returns the same flag:
+// false when a pivot is not positive, with the pose unchanged.
+//
+// Bound by issue: one wave on its own issues an instruction every 8 cycles,
+// so what counts is the number of instructions.  Every lane does the whole
+// factorisation in its own registers (65 multiply-adds); a row to a lane
+// costs two readlanes for each pivot entry, and their waits.  The update
+// takes a column of T to a lane and applies exp to it as vector products (a
+// lane for each entry needs its row of R and V picked by selects).
 __device__ inline bool solve_update_wave(const double* ne, double damping, double* pose) {
     const int lane = threadIdx.x & 63;
-    const int i = lane < 6 ? lane : 5;  // lanes 6.. shadow row 5; their values are never read
+    double A[21], x[6], inv[6];
+#pragma unroll
+    for (int k = 0; k < 21; ++k) A[k] = ne[k];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) x[k] = -ne[21 + k];
+    double T[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) T[r] = pose[4 * r + (lane & 3)];
     double tr = 0.0;
 #pragma unroll
-    for (int d = 0; d < 6; ++d) tr += ne[upper_index(d, d)];
+    for (int d = 0; d < 6; ++d) tr += A[upper_index(d, d)];
     const double mu = damping * tr * (1.0 / 6.0);
-    double row[7];
 #pragma unroll
-    for (int c = 0; c < 6; ++c) {
-        const double h = ne[i <= c ? upper_index(i, c) : upper_index(c, i)];
-        row[c] = c == i ? h + mu : h;
-    }
-    row[6] = -ne[21 + i];
-    double inv_piv[6];
+    for (int d = 0; d < 6; ++d) A[upper_index(d, d)] += mu;
     bool ok = true;
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
-        double pr[7];
+        const double d = A[upper_index(j, j)];
+        ok = ok && d > 0.0;
+        inv[j] = recip(d);
 #pragma unroll
-        for (int c = j; c < 7; ++c) pr[c] = bcast_lane(row[c], j);
-        ok = ok && pr[j] > 0.0;
-        inv_piv[j] = recip(pr[j]);
-        const double f = lane > j ? row[j] * inv_piv[j] : 0.0;
+        for (int i = j + 1; i < 6; ++i) {
+            const double f = A[upper_index(j, i)] * inv[j];
 #pragma unroll
-        for (int c = j + 1; c < 7; ++c) row[c] = fma(-f, pr[c], row[c]);
+            for (int c = i; c < 6; ++c) A[upper_index(i, c)] = fma(-f, A[upper_index(j, c)], A[upper_index(i, c)]);
+            x[i] = fma(-f, x[j], x[i]);
+        }
     }
     if (!ok) return false;
-    double x[6];
-    double rhs = row[6];
 #pragma unroll
-    for (int c = 5; c >= 0; --c) {
-        x[c] = bcast_lane(rhs * inv_piv[c], c);
-        rhs = fma(-row[c], x[c], rhs);
+    for (int j = 5; j >= 0; --j) {
+        x[j] *= inv[j];
+#pragma unroll
+        for (int i = 0; i < j; ++i) x[i] = fma(-A[upper_index(i, j)], x[j], x[i]);
     }
     // exp of the twist (rho, phi) = (x[0..2], x[3..5]); coefficients as in se3_exp
-    const double p0 = x[3], p1 = x[4], p2 = x[5];
-    const double th2 = p0 * p0 + p1 * p1 + p2 * p2;
-    double A, B, C;
+    const double p[3] = {x[3], x[4], x[5]}, rho[3] = {x[0], x[1], x[2]};
+    const double th2 = fma(p[0], p[0], fma(p[1], p[1], p[2] * p[2]));
+    double ca, cb, cc;
     if (th2 < 0.02 * 0.02) {
         // the series of se3_exp in Horner form with reciprocal constants
         // (a division by a constant is a ten-instruction sequence in float64)
@@ -698,39 +727,24 @@ __device__ inline bool solve_update_wave(const double* ne, double damping, doubl
         constexpr double b1 = -1.0 / 24.0, b2 = 1.0 / 720.0, b3 = -1.0 / 40320.0, b4 = 1.0 / 3628800.0;
         constexpr double c0 = 1.0 / 6.0, c1 = -1.0 / 120.0, c2 = 1.0 / 5040.0, c3 = -1.0 / 362880.0,
                          c4 = 1.0 / 39916800.0;
-        A = 1.0 + th2 * (a1 + th2 * (a2 + th2 * (a3 + th2 * a4)));
-        B = 0.5 + th2 * (b1 + th2 * (b2 + th2 * (b3 + th2 * b4)));
-        C = c0 + th2 * (c1 + th2 * (c2 + th2 * (c3 + th2 * c4)));
+        ca = 1.0 + th2 * (a1 + th2 * (a2 + th2 * (a3 + th2 * a4)));
+        cb = 0.5 + th2 * (b1 + th2 * (b2 + th2 * (b3 + th2 * b4)));
+        cc = c0 + th2 * (c1 + th2 * (c2 + th2 * (c3 + th2 * c4)));
     } else {
         const double th = sqrt(th2);
         const double sn = sin(th), cs = cos(th);
-        A = sn / th;
-        B = (1.0 - cs) / th2;
-        C = (th - sn) / (th2 * th);
+        ca = sn / th;
+        cb = (1.0 - cs) / th2;
+        cc = (th - sn) / (th2 * th);
     }
-    if (lane < 12) {
-        const int r = lane >> 2, col = lane & 3;
-        // row r of K = phi^ and of K^2 = phi phi^T - th2 I
-        const double pr_ = r == 0 ? p0 : (r == 1 ? p1 : p2);
-        const double k0 = r == 0 ? 0.0 : (r == 1 ? p2 : -p1);
-        const double k1 = r == 0 ? -p2 : (r == 1 ? 0.0 : p0);
-        const double k2 = r == 0 ? p1 : (r == 1 ? -p0 : 0.0);
-        const double q0 = pr_ * p0 - (r == 0 ? th2 : 0.0);
-        const double q1 = pr_ * p1 - (r == 1 ? th2 : 0.0);
-        const double q2 = pr_ * p2 - (r == 2 ? th2 : 0.0);
-        const double R0 = (r == 0 ? 1.0 : 0.0) + A * k0 + B * q0;
-        const double R1 = (r == 1 ? 1.0 : 0.0) + A * k1 + B * q1;
-        const double R2 = (r == 2 ? 1.0 : 0.0) + A * k2 + B * q2;
-        double out = R0 * pose[col] + R1 * pose[4 + col] + R2 * pose[8 + col];
-        if (col == 3) {
-            const double V0 = (r == 0 ? 1.0 : 0.0) + B * k0 + C * q0;
-            const double V1 = (r == 1 ? 1.0 : 0.0) + B * k1 + C * q1;
-            const double V2 = (r == 2 ? 1.0 : 0.0) + B * k2 + C * q2;
-            out += V0 * x[0] + V1 * x[1] + V2 * x[2];
-        }
-        // every lane's reads of the pose above precede this store (the store
-        // depends on them, and the wave issues LDS operations in order)
-        pose[lane] = out;
+    double dT[3], dr[3];
+    twist_apply(p, th2, ca, cb, T, dT);
+    twist_apply(p, th2, cb, cc, rho, dr);
+    // every lane's reads of the pose above precede these stores (the stores
+    // depend on them, and the wave issues LDS operations in order)
+    if (lane < 4) {
+#pragma unroll
+        for (int r = 0; r < 3; ++r) pose[4 * r + lane] = T[r] + (dT[r] + (lane == 3 ? rho[r] + dr[r] : 0.0));
     }
     return true;
 }
@@ -776,10 +790,12 @@ __device__ inline void complete_device_stores() { __builtin_amdgcn_s_waitcnt(0);
 // consecutive, and the leaves of a level are numbered 0 .. nleaf-1 without
 // gaps.  Partials and leaf sums are tagged with their iteration (below),
 // the leader polls its leaf's partials, and every member polls the leaf
-// sums.  Sync words: the tickets, the iteration count of the pose published
-// at level boundaries for work-groups that join, an abort flag, and each
-// tracking leaf leader's XCC id.  The pyramid
-// kernel clears them and the tagged words before each tracking launch.
+// sums.  A small level (below) is worked by one XCD alone, with no leaves.
+// Sync words: the tickets, an abort flag, each tracking leaf leader's XCC id,
+// and, in the place of the tickets (which tracking does not take), the XCC id
+// of each work-group of a one-XCD level.  The pose published at level
+// boundaries for work-groups that join follows the two sets.  The pyramid
+// kernel clears all of these before each tracking launch.
 constexpr int kLeaf = 16;
 constexpr int kMaxLeaves = kMaxGroups / kLeaf;
 constexpr int kPerXcd = kMaxGroups / kXcds;
@@ -796,6 +812,8 @@ __device__ inline int xcd_leaves(int n) {
     return kXcds * (n / span) + min(kXcds, n % span);
 }
 // one set of partials: a partial per work-group, then one per leaf
+constexpr int kXcdMembers = 32;   // work-groups of a one-XCD level (the CUs of an XCD)
+constexpr int kPoseWords = 24;    // the published pose: 32 bits of it and the iteration count to a word
 constexpr size_t kPartsPerSet = (size_t)(kMaxGroups + kMaxLeaves) * kPartStride;
 // Leaf tickets are kTicketStride words (256 B) apart: device-scope atomics
 // on one cache line share the memory-side atomic unit.
@@ -803,10 +821,10 @@ constexpr int kTicketStride = 64;
 enum {
     kSyncLeaf = 0,                                          // [2][kMaxLeaves] x kTicketStride
     kSyncRoot = kSyncLeaf + 2 * kMaxLeaves * kTicketStride,  // [2]
-    kSyncPub = kSyncRoot + 2,                               // iterations reflected by the published pose
-    kSyncAbort = kSyncPub + 1,
+    kSyncAbort = kSyncRoot + 2,
     kSyncXcc = kSyncAbort + 1,                              // [kMaxLeaves] 1 + XCC id of each tracking leaf leader
-    kSyncWords = kSyncXcc + kMaxLeaves
+    kSyncWords = kSyncXcc + kMaxLeaves,
+    kSyncMember = kSyncLeaf                                 // [kXcdMembers] 1 + XCC id, one-XCD levels
 };
 
 // Arrival, thread 0 only.  leaf_arrive: true for the last of the kLeaf
@@ -884,29 +902,38 @@ __device__ inline bool reduce_tree(const float acc[kNE], const float cmp[kNE], d
 }
 
 // The sum of n tagged partials (consecutive, kPartStride apart) of the
-// iteration tagged `tag`, in the order of total_partials (thread (k, p) adds
-// entry k of the partials p, p+8, ...), each word polled until it carries
-// the tag.  Result in r.tot; false (in every thread) on timeout or when
-// another work-group aborted.
-template <bool COMP>
+// iteration tagged `tag`: thread (k, p) of LANES to an entry adds entry k of
+// the partials p, p + LANES, ..., F of them in flight, each word polled until
+// it carries the tag, and the sums of an entry are added across lanes (COMP:
+// in order, through LDS).  Result in r.tot; false (in every thread) on timeout or when another
+// work-group aborted.  With `leaf` the result is stored there instead, tagged
+// (device scope), and what failed shows in the next sum, whose barrier it
+// takes.  `buf` (1 or 2): the part of the LDS that the sum takes, another
+// than the sum's before it.
+template <bool COMP, int F, int LANES = 8>
 __device__ inline bool total_leaves(const double* leafpart, int nleaf, unsigned long long tag, const unsigned* sync,
-                                    unsigned max_polls, ReduceLds& r) {
-    bool ok = true;
-    if (threadIdx.x < kNE * 8) {
-        const int k = threadIdx.x >> 3, p = threadIdx.x & 7;
+                                    unsigned max_polls, ReduceLds& r, int buf, double* leaf = nullptr) {
+    static_assert(!COMP || LANES == 8, "the compensated sum keeps its order");
+    if (threadIdx.x < kNE * LANES) {
+        const int k = threadIdx.x / LANES, p = threadIdx.x % LANES;
         double s = 0.0;
         Kahan ks;
-        for (int b0 = p; b0 < nleaf && ok; b0 += 16) {
-            const int b1 = b0 + 8;
-            const unsigned long long* w0 =
-                reinterpret_cast<const unsigned long long*>(&leafpart[(size_t)b0 * kPartStride + k]);
-            const unsigned long long* w1 =
-                reinterpret_cast<const unsigned long long*>(&leafpart[(size_t)(b1 < nleaf ? b1 : b0) * kPartStride + k]);
-            unsigned long long x0 = __hip_atomic_load(w0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            unsigned long long x1 =
-                b1 < nleaf ? __hip_atomic_load(w1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tag;
+        bool ok = true;
+        for (int b0 = p; b0 < nleaf && ok; b0 += LANES * F) {
+            const unsigned long long* w[F];
+            unsigned long long x[F];
+#pragma unroll
+            for (int j = 0; j < F; ++j) {
+                const int b = b0 + LANES * j;
+                w[j] = reinterpret_cast<const unsigned long long*>(&leafpart[(size_t)(b < nleaf ? b : b0) * kPartStride + k]);
+                x[j] = b < nleaf ? __hip_atomic_load(w[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tag;
+            }
             unsigned spins = 0;
-            while ((x0 & kTagMask) != tag || (x1 & kTagMask) != tag) {
+            for (;;) {
+                bool have = true;
+#pragma unroll
+                for (int j = 0; j < F; ++j) have = have && (x[j] & kTagMask) == tag;
+                if (have) break;
                 if (++spins > max_polls ||
                     ((spins & 255u) == 0u &&
                      __hip_atomic_load(&sync[kSyncAbort], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
@@ -914,34 +941,46 @@ __device__ inline bool total_leaves(const double* leafpart, int nleaf, unsigned 
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);
-                if ((x0 & kTagMask) != tag) x0 = __hip_atomic_load(w0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if ((x1 & kTagMask) != tag) x1 = __hip_atomic_load(w1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int j = 0; j < F; ++j)
+                    if ((x[j] & kTagMask) != tag)
+                        x[j] = __hip_atomic_load(w[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (COMP) {
-                ks.add((float)untag_word(x0));
-                if (b1 < nleaf) ks.add((float)untag_word(x1));
-            } else {
-                s += untag_word(x0);
-                if (b1 < nleaf) s += untag_word(x1);
+#pragma unroll
+            for (int j = 0; j < F; ++j) {
+                if (b0 + LANES * j >= nleaf) break;
+                if (COMP) ks.add((float)untag_word(x[j])); else s += untag_word(x[j]);
             }
         }
-        r.part[k][p] = COMP ? (double)ks.value() : s;
-    }
-    if (__syncthreads_or(ok ? 0 : 1)) return false;
-    if (threadIdx.x < kNE) {
-        const int k = threadIdx.x;
+        if (!ok) r.fail = 1;
         if (COMP) {
-            Kahan ks;
-            for (int p = 0; p < 8; ++p) ks.add((float)r.part[k][p]);
-            r.tot[k] = (double)ks.value();
+            r.part[buf][k][p] = (double)ks.value();
         } else {
-            double t = 0.0;
-            for (int p = 0; p < 8; ++p) t += r.part[k][p];
-            r.tot[k] = t;
+            s = lane_sum<LANES>(s);
+            if (__all(ok) && p == 0) {
+                if (leaf)
+                    store_entry(leaf, k, s, tag, false);
+                else
+                    r.tot[k] = s;
+            }
         }
     }
+    if (COMP) {
+        __syncthreads();
+        if (r.fail) return false;
+        if (threadIdx.x < kNE) {
+            const int k = threadIdx.x;
+            Kahan ks;
+            for (int p = 0; p < 8; ++p) ks.add((float)r.part[buf][k][p]);
+            if (leaf)
+                store_entry(leaf, k, (double)ks.value(), tag, false);
+            else
+                r.tot[k] = (double)ks.value();
+        }
+    }
+    if (leaf) return true;
     __syncthreads();
-    return true;
+    return !r.fail;
 }
 
 // A member's share of an iteration of the tracking kernel (members are
@@ -960,26 +999,44 @@ __device__ inline bool contribute(const float acc[kNE], const float cmp[kNE], do
     if (!xcd_leader(b)) return true;
     const int leaf = xcd_leaf(b);
     const int leaf_size = min(kXcdLeaf, (groups - b + kXcds - 1) / kXcds);
-    if (!total_leaves<COMP>(mine, leaf_size, tag, sync, max_polls, r)) return false;
-    // r.tot holds the leaf sum in every thread; lanes of wave 0 store it
-    if (threadIdx.x < kNE)
-        __hip_atomic_store(reinterpret_cast<unsigned long long*>(&leafpart[(size_t)leaf * kPartStride + threadIdx.x]),
-                           tag_word(r.tot[threadIdx.x], tag), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
+    return total_leaves<COMP, 2>(mine, leaf_size, tag, sync, max_polls, r, 1, leafpart + (size_t)leaf * kPartStride);
 }
 
-// Wait (thread 0 only) until the sync word `word` reaches `target`;
-// device-scope polling with a short sleep.  Returns false on timeout or when
+// The pose at a level boundary, for the work-groups that join: words of 32
+// bits of it beside the count of iterations it reflects (so each word tells
+// by itself that it is there: one trip through memory instead of the pose's
+// and then a flag's).  publish_pose: by one work-group.  take_pose: polls
+// them into the pose in LDS; false (in every thread) on timeout or when
 // another work-group aborted.
-__device__ inline bool wait_done(unsigned* sync, int word, unsigned target, unsigned max_polls) {
-    unsigned spins = 0;
-    while (__hip_atomic_load(&sync[word], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-        if (++spins > max_polls ||
-            __hip_atomic_load(&sync[kSyncAbort], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            return false;
-        __builtin_amdgcn_s_sleep(2);
+__device__ inline void publish_pose(unsigned long long* pub, unsigned iters, const double* pose) {
+    if (threadIdx.x < kPoseWords) {
+        const unsigned bits = reinterpret_cast<const unsigned*>(pose)[threadIdx.x];
+        __hip_atomic_store(&pub[threadIdx.x], ((unsigned long long)bits << 32) | iters, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     }
-    return true;
+}
+__device__ inline bool take_pose(const unsigned long long* pub, const unsigned* sync, unsigned iters,
+                                 unsigned max_polls, double* pose, ReduceLds& r) {
+    __syncthreads();   // the pose that it replaces has been read
+    if (threadIdx.x < kPoseWords) {
+        unsigned long long x;
+        unsigned spins = 0;
+        bool ok = true;
+        while ((unsigned)(x = __hip_atomic_load(&pub[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != iters) {
+            if (++spins > max_polls ||
+                __hip_atomic_load(&sync[kSyncAbort], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                ok = false;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(2);
+        }
+        if (ok)
+            reinterpret_cast<unsigned*>(pose)[threadIdx.x] = (unsigned)(x >> 32);
+        else
+            r.fail = 1;
+    }
+    __syncthreads();
+    return !r.fail;
 }
 
 // Work-groups that take part at a level: about kPixPerGroup pixels each,
@@ -989,10 +1046,33 @@ __device__ inline bool wait_done(unsigned* sync, int word, unsigned target, unsi
 // level; 64 at the coarsest level, or 128 at the middle one, are slower.
 constexpr int kPixPerGroup = 256;
 constexpr int kMinGroups = 128;
-__device__ inline int level_groups(const TrackLevel& L, int G) {
-    int g = (L.W * L.H + kPixPerGroup - 1) / kPixPerGroup;
+// A level of at most kOneXcdPixels is worked by the work-groups of one XCD
+// (b mod 8 = 0), each of which adds all of their partials itself: one hop
+// through that XCD's L2 (0.46 us) instead of two hops, the second between
+// XCDs (1.2 us).  Above it the pixels' own time on 32 CUs outgrows what the
+// hop saves: an iteration takes 3.4 us against 5.0 at 1200 pixels, 4.5
+// against 5.0 at 19200, and at 57600 would take three pixels a thread more
+// where the whole grid takes 5.2.  The plain Taylor form only (`one`): the compensated sums keep
+// their grouping, and the tri-linear form's pixels cost several times as
+// much.  Where some levels go to one XCD the others take the whole grid, so
+// that every work-group of a level is also in the next one: a work-group
+// still reading the last partials of its level then contributes to the next
+// before anyone overwrites them.
+constexpr int kOneXcdPixels = 24576;
+struct LevelPlan {
+    int groups;
+    bool one;
+};
+__device__ inline LevelPlan level_plan(const TrackLevel& L, int G, bool one) {
+    const int npx = L.W * L.H;
+    if (one && npx <= kOneXcdPixels) return {min(kXcdMembers, (G + kXcds - 1) / kXcds), true};
+    if (one) return {G, false};
+    int g = (npx + kPixPerGroup - 1) / kPixPerGroup;
     g = g < kMinGroups ? kMinGroups : g;
-    return g > G ? G : g;
+    return {g > G ? G : g, false};
+}
+__device__ inline bool level_member(const LevelPlan& p, int b) {
+    return p.one ? b % kXcds == 0 && b / kXcds < p.groups : b < p.groups;
 }
 
 // Rank in the image of member b of n: the members split the level's pixels
@@ -1006,7 +1086,7 @@ __device__ inline int level_groups(const TrackLevel& L, int G) {
 // Only the members of a level (the first Gl work-groups) run its
 // iterations; a work-group that joins at a later level takes the pose that
 // work-group 0 publishes at the end of the previous level (it publishes only
-// when the next level has more members).  Buffer reuse: partials and leaf
+// when the next level has other members).  Buffer reuse: partials and leaf
 // sums alternate between two sets by iteration parity.  A member writes set
 // (gi & 1) again at gi + 2 only after it has seen every leaf sum of gi + 1;
 // each of those was published after its leaf's members had contributed to
@@ -1020,25 +1100,34 @@ __global__ __launch_bounds__(kTrackBlock) void k_track_frame(MapView M, TrackArg
                                                               double* pose_out, double* partials, unsigned* sync,
                                                               float* stats, int32_t* status) {
     __shared__ double s_pose[12];
-    __shared__ int s_ok, s_local;
+    __shared__ int s_local;
     __shared__ ReduceLds red;
     __shared__ float s_depth[kTrackBatch * kTrackBlock];
     constexpr bool COMP = STORAGE == GSDF_BF16 || STORAGE == GSDF_FP16;
-    const int G = gridDim.x;
-    double* pose_pub = partials + 2 * kPartsPerSet;
+    constexpr bool kOneXcd = STORAGE == GSDF_FP32 && MODEL == GSDF_MODEL_TAYLOR;
+    const int G = gridDim.x, b = blockIdx.x;
+    unsigned long long* pose_pub = reinterpret_cast<unsigned long long*>(partials + 2 * kPartsPerSet);
     // a work-group that takes part in no level holds nothing anyone needs
-    int span = 1;
+    bool any = b == 0;
     for (int l = 0; l < a.levels; ++l)
-        if (a.iters[l] > 0) span = max(span, level_groups(a.lv[l], G));
-    if ((int)blockIdx.x >= span) return;
-    // the leaders publish their XCD; a member compares it with its own
-    // before its first partial (at that point the leader's store has long
-    // been visible, so the comparison costs one load)
-    const bool leader = xcd_leader(blockIdx.x);
-    if (leader && threadIdx.x == 0)
-        __hip_atomic_store(&sync[kSyncXcc + xcd_leaf(blockIdx.x)], xcc_id() + 1u, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+        if (a.iters[l] > 0) any = any || level_member(level_plan(a.lv[l], G, kOneXcd), b);
+    if (!any) return;
+    // the leaders, and the work-groups of a one-XCD level, publish their
+    // XCD; the others compare it with their own before their first partial
+    // (at that point the store has long been visible, so the comparison
+    // costs one load)
+    const bool leader = xcd_leader(b);
+    if (threadIdx.x == 0) {
+        red.fail = 0;
+        if (leader)
+            __hip_atomic_store(&sync[kSyncXcc + xcd_leaf(b)], xcc_id() + 1u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        if (kOneXcd && b % kXcds == 0 && b / kXcds < kXcdMembers)
+            __hip_atomic_store(&sync[kSyncMember + b / kXcds], xcc_id() + 1u, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
     int local = a.device_scope ? 0 : (leader ? 1 : -1);   // -1: not known yet
+    int local_one = a.device_scope ? 0 : -1;
     // pose_in may be pose_out: every work-group still running reads it here,
     // before its first contribution, and work-group 0 writes the result only
     // after the last iteration, which needs all of those contributions
@@ -1053,34 +1142,36 @@ __global__ __launch_bounds__(kTrackBlock) void k_track_frame(MapView M, TrackArg
     }
     int gi = 0;           // global iteration index
     int have = 0;         // iterations the pose in s_pose reflects
+    // the counters, statistics and checks of work-group 0 are its last
+    // wave's: on the solving wave they held every iteration up by 0.25 us
+    const bool counts = b == 0 && threadIdx.x == kTrackBlock - 64;
+    unsigned long long n_valid = 0, n_used = 0;
+    double damping = a.damping;
+    asm("" : "+v"(damping));   // in registers: a load from the arguments would stand in every solve
     // per-iteration stamps (work-group 0, thread 0), when asked for
     const bool stamp = a.clocks && blockIdx.x == 0 && threadIdx.x == 0;
     const unsigned long long t0 = stamp ? wall_clock64() : 0ull;
     for (int l = a.levels - 1; l >= 0; --l) {
         if (a.iters[l] == 0) continue;
         const TrackLevel L = a.lv[l];
-        const int Gl = level_groups(L, G);
+        const LevelPlan plan = level_plan(L, G, kOneXcd);
+        const int Gl = plan.groups;
         const int nleaf = xcd_leaves(Gl);
-        if ((int)blockIdx.x >= Gl) {
+        if (!level_member(plan, b)) {
             // not a member: skip the level
             gi += a.iters[l];
             continue;
         }
         if (have < gi) {
             // joining: take the pose published at the end of the previous level
-            if (threadIdx.x == 0) s_ok = wait_done(sync, kSyncPub, (unsigned)gi, a.join_polls) ? 1 : 0;
-            __syncthreads();
-            if (!s_ok) {
+            if (!take_pose(pose_pub, sync, (unsigned)gi, a.join_polls, s_pose, red)) {
+                // (never work-group 0, a member of every level)
                 if (threadIdx.x == 0) {
                     __hip_atomic_store(&sync[kSyncAbort], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     raise_status(status, GSDF_EHIP);
                 }
                 return;
             }
-            if (threadIdx.x < 12)
-                s_pose[threadIdx.x] =
-                    __hip_atomic_load(&pose_pub[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __syncthreads();
             have = gi;
         }
         // a member's pixels are one contiguous chunk of the level, the same
@@ -1089,7 +1180,7 @@ __global__ __launch_bounds__(kTrackBlock) void k_track_frame(MapView M, TrackArg
         // wrote)
         const int npx = L.W * L.H;
         const int chunk = (npx + Gl - 1) / Gl;
-        const int c0 = min(band_rank(blockIdx.x, Gl) * chunk, npx);
+        const int c0 = min((plan.one ? b / kXcds : band_rank(b, Gl)) * chunk, npx);
         const int c1 = min(c0 + chunk, npx);
         const int first = c0 + threadIdx.x;
 #pragma unroll
@@ -1110,25 +1201,39 @@ __global__ __launch_bounds__(kTrackBlock) void k_track_frame(MapView M, TrackArg
                 accumulate<STORAGE>(M, L, a, P, first, kTrackBlock, c1, s_depth, acc, cmp);
             const unsigned long long tag = (unsigned long long)(gi + 1);
             if (stamp) a.clocks[4 * gi] = wall_clock64() - t0;
-            if (local < 0) {
-                // on the leader's XCD?  A bounded wait; if it ends without an
-                // answer the partials simply go through device scope
-                if (threadIdx.x == 0) {
-                    const unsigned* w = &sync[kSyncXcc + xcd_leaf(blockIdx.x)];
+            // on the reader's XCD?  A bounded wait; if it ends without an
+            // answer the partials simply go through device scope
+            int& here = plan.one ? local_one : local;
+            if (here < 0) {
+                if (threadIdx.x < 64) {
+                    const unsigned* w = plan.one ? &sync[kSyncMember + min((int)threadIdx.x, Gl - 1)]
+                                                 : &sync[kSyncXcc + xcd_leaf(b)];
                     unsigned v, spins = 0;
                     while ((v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0u &&
                            ++spins <= a.tag_polls)
                         __builtin_amdgcn_s_sleep(1);
-                    s_local = v == xcc_id() + 1u ? 1 : 0;
+                    const bool all = __all(v == xcc_id() + 1u);
+                    if (threadIdx.x == 0) s_local = all ? 1 : 0;
                 }
                 __syncthreads();
-                local = s_local;
+                here = s_local;
             }
-            // every member: the same sum of the leaf sums, the same solve
-            const bool part_ok =
-                contribute<COMP>(acc, cmp, part, leafpart, Gl, sync, a.tag_polls, red, tag, local != 0);
+            // every member: the same sum (of all partials, or of the leaf
+            // sums), the same solve
+            bool part_ok = true;
+            if (plan.one)
+                store_partial<COMP>(acc, cmp, part + (size_t)(b / kXcds) * kPartStride, red, tag, here != 0);
+            else
+                part_ok = contribute<COMP>(acc, cmp, part, leafpart, Gl, sync, a.tag_polls, red, tag, here != 0);
             if (stamp) a.clocks[4 * gi + 1] = wall_clock64() - t0;
-            if (!part_ok || !total_leaves<COMP>(leafpart, nleaf, tag, sync, a.tag_polls, red)) {
+            if (part_ok)
+                part_ok = plan.one ? total_leaves<COMP, 2, COMP ? 8 : 16>(part, Gl, tag, sync, a.tag_polls, red, 2)
+                                   : total_leaves<COMP, 2>(leafpart, nleaf, tag, sync, a.tag_polls, red, 2);
+            if (!part_ok) {
+                if (counts) {
+                    add_stat(M, kStatTrackValid, n_valid);
+                    add_stat(M, kStatTrackUsed, n_used);
+                }
                 if (threadIdx.x == 0) {
                     __hip_atomic_store(&sync[kSyncAbort], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     raise_status(status, GSDF_EHIP);
@@ -1137,43 +1242,41 @@ __global__ __launch_bounds__(kTrackBlock) void k_track_frame(MapView M, TrackArg
             }
             if (stamp) a.clocks[4 * gi + 2] = wall_clock64() - t0;
             if (threadIdx.x < 64) {
-                const bool solved = solve_update_wave(red.tot, a.damping, s_pose);
-                if (blockIdx.x == 0 && threadIdx.x == 0) {
-                    const double* t = red.tot;
-                    if (!solved) raise_status(status, GSDF_ENOTPD);
-                    if (l == 0 && it == a.iters[0] - 1 && t[28] < (double)a.min_inlier_frac * t[29])
-                        raise_status(status, GSDF_ELOST);
-                    if (stats) {
-                        stats[2 * gi] = (float)t[27];
-                        stats[2 * gi + 1] = (float)t[28];
-                    }
-                    add_stat(M, kStatTrackValid, (unsigned long long)t[29]);
-                    add_stat(M, kStatTrackUsed, (unsigned long long)t[28]);
-                    if (stamp) a.clocks[4 * gi + 3] = wall_clock64() - t0;
-                }
+                const bool solved = solve_update_wave(red.tot, damping, s_pose);
+                if (!solved && b == 0 && threadIdx.x == 0) raise_status(status, GSDF_ENOTPD);
+                if (stamp) a.clocks[4 * gi + 3] = wall_clock64() - t0;
             }
             __syncthreads();
+            // by another wave than the one that solves (red.tot is next
+            // written after two more barriers)
+            if (counts) {
+                const double* t = red.tot;
+                if (l == 0 && it == a.iters[0] - 1 && t[28] < (double)a.min_inlier_frac * t[29])
+                    raise_status(status, GSDF_ELOST);
+                if (stats) {
+                    stats[2 * gi] = (float)t[27];
+                    stats[2 * gi + 1] = (float)t[28];
+                }
+                n_valid += (unsigned long long)t[29];
+                n_used += (unsigned long long)t[28];
+            }
         }
         have = gi;
         // publish for the work-groups that join at the next level
-        int next_groups = 0;
-        for (int n = l - 1; n >= 0; --n)
-            if (a.iters[n] > 0) {
-                next_groups = level_groups(a.lv[n], G);
+        if (b == 0) {
+            for (int n = l - 1; n >= 0; --n) {
+                if (a.iters[n] == 0) continue;
+                const LevelPlan next = level_plan(a.lv[n], G, kOneXcd);
+                if (next.groups > Gl || next.one != plan.one) publish_pose(pose_pub, (unsigned)gi, s_pose);
                 break;
-            }
-        if (blockIdx.x == 0 && next_groups > Gl) {
-            if (threadIdx.x < 12)
-                __hip_atomic_store(&pose_pub[threadIdx.x], s_pose[threadIdx.x], __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                complete_device_stores();
-                __hip_atomic_store(&sync[kSyncPub], (unsigned)gi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     }
-    if (blockIdx.x == 0 && threadIdx.x < 12) pose_out[threadIdx.x] = s_pose[threadIdx.x];
+    if (b == 0 && threadIdx.x < 12) pose_out[threadIdx.x] = s_pose[threadIdx.x];
+    if (counts) {
+        add_stat(M, kStatTrackValid, n_valid);
+        add_stat(M, kStatTrackUsed, n_used);
+    }
 }
 
 // One linearisation (gsdf_normal_equations): a single launch whose last
@@ -1284,7 +1387,7 @@ struct PyramidArgs {
     float zmin, zmax, Tf;
     unsigned* sync;
     unsigned long long* sets[2];   // tagged partials and leaf sums of the two sets (null: none)
-    int part_words;                // words of the work-group partials of a set to clear
+    int per_xcd;                   // work-groups of each XCD whose partials are cleared
 };
 
 __device__ inline float pyr_combine(float a, float b, float c, float e, const PyramidArgs& p) {
@@ -1305,13 +1408,20 @@ __global__ __launch_bounds__(256) void k_pyramid(PyramidArgs p) {
         // words and tagged words
         const int nthreads = gridDim.x * gridDim.y * blockDim.x;
         const int tid = (blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-        for (int k = tid; k < kSyncWords; k += nthreads) p.sync[k] = 0u;
-        if (p.sets[0]) {
-            // the partials of the work-groups that run, then every leaf sum
+        if (!p.sets[0]) {
+            for (int k = tid; k < kSyncWords; k += nthreads) p.sync[k] = 0u;
+        } else {
+            // the sync words that tracking uses, the partials of the
+            // work-groups that run (p.per_xcd of each XCD), every leaf sum
+            for (int k = tid; k < kXcdMembers + kSyncWords - kSyncRoot; k += nthreads)
+                p.sync[k < kXcdMembers ? kSyncMember + k : kSyncRoot + (k - kXcdMembers)] = 0u;
+            if (tid < kPoseWords) p.sets[0][2 * kPartsPerSet + tid] = 0ull;
             constexpr int kLeafWords = kMaxLeaves * kPartStride;
-            for (int k = tid; k < p.part_words + kLeafWords; k += nthreads) {
-                const size_t w = k < p.part_words ? (size_t)k
-                                                  : (size_t)kMaxGroups * kPartStride + (size_t)(k - p.part_words);
+            const int xcd_words = p.per_xcd * kPartStride;
+            for (int k = tid; k < kXcds * xcd_words + kLeafWords; k += nthreads) {
+                const int x = k / xcd_words;
+                const size_t w = x < kXcds ? (size_t)x * kPerXcd * kPartStride + (size_t)(k - x * xcd_words)
+                                           : (size_t)kMaxGroups * kPartStride + (size_t)(k - kXcds * xcd_words);
                 p.sets[0][w] = 0ull;
                 p.sets[1][w] = 0ull;
             }
@@ -1359,7 +1469,7 @@ inline ScratchLayout scratch_layout(const gsdf_camera& c, int levels) {
     ScratchLayout s;
     size_t o = 0;
     s.sync = o;     o = align256(o + kSyncWords * 4);
-    s.partials = o; o = align256(o + (2 * kPartsPerSet + 16) * 8);  // two sets, then the published pose
+    s.partials = o; o = align256(o + (2 * kPartsPerSet + kPoseWords) * 8);  // two sets, then the published pose
     int W = c.width, H = c.height;
     s.level[0] = 0;
     for (int l = 1; l < 4; ++l) {
@@ -1538,7 +1648,7 @@ int track_frame_on(const gsdf_map* map, const float* depth_dev, const gsdf_camer
         p.sync = sync;
         for (int q = 0; q < 2; ++q)
             p.sets[q] = reinterpret_cast<unsigned long long*>(partials + (size_t)q * kPartsPerSet);
-        p.part_words = kMaxGroups * kPartStride;
+        p.per_xcd = ceil_div(track_groups(), kXcds);
         TimedLaunch tp(map->timer, GSDF_K_PYRAMID, s);
         // a single level has no pyramid work: enough work-groups for the clearing
         dim3 grd(levels > 1 ? ceil_div(a.lv[1].W, 16) : 32, levels > 1 ? ceil_div(a.lv[1].H, 16) : 1);
