@@ -50,6 +50,8 @@ constexpr int kAdjTile = 32;        // the pixel passes take 32x32 pixel tiles, 
 constexpr int kScanTile = 4096;     // block counts per work-group of the offset scan
 constexpr int kScanBlock = 1024;    // threads of the offset scan
 constexpr int kTilePx = kAdjTile * kAdjTile;
+constexpr int kCountBits = 10;      // of a record's count less one; the place above (below 2^31 / kTilePx)
+static_assert(kTilePx == 1 << kCountBits, "a record's two numbers");
 constexpr int kGatherBatch = 2;     // list entries a lane of the gather loads at a time
 constexpr int kLookup = 2;          // pixels a thread of the pixel passes looks up together
 // Pixels to a piece of the gather: a 2048th of the pixels of all keyframes (two
@@ -70,13 +72,14 @@ struct AdjArgs {
 // sums, the keyframe poses exp(xi^) T0, two words of bounds (the reach of a
 // frozen association as float64 bits, max |s_i|), and the pixel lists:
 // per tile (K x tiles of them) 1024 list entries (pixel of the tile, depth) and up
-// to 1024 records
-// (block, count), the records' count per tile, the runs (start, count)
-// sorted by block, and per block its pixel count, run count, first run and
-// a cursor, with the per-tile sums of the scan.  Then what the gather needs to
+// to 1024 records (block; its count of pixels and the record's place among
+// the block's), the records' count per tile, the runs (start, count) sorted
+// by block, and per block its tally (runs in the low word, pixels in the
+// high: one atomic counts both) and first run, with the per-tile sums of the
+// scan.  Then what the gather needs to
 // take a block in parts.
 struct AdjScratch {
-    size_t partials, poses, bounds, list, recs, nrec, runs, pix_count, run_count, run_off, cursor, tiles, total;
+    size_t partials, poses, bounds, list, recs, nrec, runs, tally, run_off, tiles, total;
     // the gather's pieces (a caller whose scratch ends at `total` has every
     // block gathered whole)
     size_t tile_sums, items, done, buffers, split_total;
@@ -101,10 +104,9 @@ inline AdjScratch adj_scratch(int32_t K, int64_t tiles, int64_t param_blocks) {
     L.recs = o;      o = align256(o + n * sizeof(int2));
     L.nrec = o;      o = align256(o + regions * sizeof(int32_t));
     L.runs = o;      o = align256(o + n * sizeof(int2));
-    L.pix_count = o; o = align256(o + nb * sizeof(int32_t));
-    L.run_count = o; o = align256(o + nb * sizeof(int32_t));
+    L.tally = o;     o = align256(align256(o + nb * sizeof(int32_t)) + nb * sizeof(int32_t));
     L.run_off = o;   o = align256(o + nb * sizeof(int32_t));
-    L.cursor = o;    o = align256(o + nb * sizeof(int32_t));
+    o = align256(o + nb * sizeof(int32_t));   // not used; keeps the sizes that callers have
     L.tiles = o;     o = align256(o + ((nb + kScanTile - 1) / kScanTile) * sizeof(int32_t));
     L.total = o;
     const int64_t piece = (int64_t)(n / kGatherShare);
@@ -133,9 +135,14 @@ __device__ inline void pixel_point(const AdjArgs& a, const double R[9], const do
     for (int r = 0; r < 3; ++r) q[r] = fma(R[3 * r], x0, fma(R[3 * r + 1], x1, fma(R[3 * r + 2], Dd, t[r])));
 }
 
-__device__ inline void nearest_voxel(const AdjArgs& a, const double q[3], int m[3]) {
+// The voxel, and its coordinates still in float64 (the same numbers where
+// they fit the block keys' range).
+__device__ inline void nearest_voxel(const AdjArgs& a, const double q[3], int m[3], double near[3]) {
 #pragma unroll
-    for (int r = 0; r < 3; ++r) m[r] = (int)floor(fma(q[r], a.inv_vs, 0.5));
+    for (int r = 0; r < 3; ++r) {
+        near[r] = floor(fma(q[r], a.inv_vs, 0.5));
+        m[r] = (int)near[r];
+    }
 }
 
 // Voxel, offsets and parameters of one pixel.
@@ -176,12 +183,13 @@ __device__ inline void lookup_batch(const MapView& M, const AdjArgs& a, const do
     float D[NP];
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
-        const size_t i = (size_t)v[j] * a.W + u[j];
+        const int i = v[j] * a.W + u[j];   // a pixel of the image when in[j]
         D[j] = in[j] ? dimg[i] : 0.0f;
         if (READ_ASSOC && in[j]) {
-            m[j][0] = aimg[3 * i];
-            m[j][1] = aimg[3 * i + 1];
-            m[j][2] = aimg[3 * i + 2];
+            const int32_t* as = aimg + 3 * (size_t)i;
+            m[j][0] = as[0];
+            m[j][1] = as[1];
+            m[j][2] = as[2];
         }
     }
     uint64_t key[NP], h[NP];
@@ -194,18 +202,21 @@ __device__ inline void lookup_batch(const MapView& M, const AdjArgs& a, const do
         if (READ_ASSOC) look[j] = look[j] && m[j][0] != INT_MIN;
         if (!look[j]) continue;
         P[j].D = D[j];
-        double q[3];
+        double q[3], near[3];
         pixel_point(a, R, t, D[j], u[j], v[j], q);
         if (READ_ASSOC) {
 #pragma unroll
-            for (int r = 0; r < 3; ++r) *reach = fmax(*reach, fabs(q[r] - a.vs * (double)m[j][r]) - 0.5 * a.vs);
+            for (int r = 0; r < 3; ++r) {
+                near[r] = (double)m[j][r];
+                *reach = fmax(*reach, fabs(q[r] - a.vs * near[r]) - 0.5 * a.vs);
+            }
         } else {
-            nearest_voxel(a, q, m[j]);
+            nearest_voxel(a, q, m[j], near);
         }
 #pragma unroll
         for (int r = 0; r < 3; ++r) {
             P[j].q[r] = (float)q[r];
-            P[j].dq[r] = (float)(q[r] - a.vs * (double)m[j][r]);
+            P[j].dq[r] = (float)(q[r] - a.vs * near[r]);
         }
         const int bx = block_of(m[j][0]), by = block_of(m[j][1]), bz = block_of(m[j][2]);
         probe[j] = key_in_range(bx, by, bz);
@@ -270,18 +281,18 @@ __device__ inline ResidualTerms residual_terms(const PixelTerm& P, float delta, 
     return o;
 }
 
-// Work-group sum of kAdjPart values per thread, in float64 (wave shuffles,
+// Work-group sum of kAdjPart values per thread, in float64 (across lanes,
 // then one value per wave in a fixed order); the totals land in out[] of
 // threads 0 .. kAdjPart-1 (out[k] in thread k).
 template <typename T>
 __device__ inline double block_sum_part(const T acc[kAdjPart], double (*s_red)[kAdjBlock / 64]) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double d[kAdjPart];
 #pragma unroll
-    for (int k = 0; k < kAdjPart; ++k) {
-        double x = (double)acc[k];
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-        if (lane == 0) s_red[k][wave] = x;
-    }
+    for (int k = 0; k < kAdjPart; ++k) d[k] = (double)acc[k];
+    static_assert(kAdjPart == 8, "wave_sum8");
+    const double y = wave_sum8(d, lane);
+    if ((lane & 7) == 0) s_red[wave_sum8_value(lane)][wave] = y;
     __syncthreads();
     double x = 0.0;
     if (threadIdx.x < kAdjPart)
@@ -362,8 +373,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_keyframe_loss(MapView M, AdjArgs 
 // Keyframe poses exp(xi^) T0 (float64), and for the adjoint the cleared
 // per-block counters and reach word.  One thread per keyframe and per block.
 __global__ void k_adj_setup(int32_t K, const double* __restrict__ T0, const double* __restrict__ xi,
-                            double* __restrict__ poses, int64_t nb, int32_t* __restrict__ pix_count,
-                            int32_t* __restrict__ run_count, int32_t* __restrict__ cursor,
+                            double* __restrict__ poses, int64_t nb, unsigned long long* __restrict__ tally,
                             int32_t* __restrict__ done, unsigned long long* __restrict__ reach) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < K) {
@@ -373,9 +383,7 @@ __global__ void k_adj_setup(int32_t K, const double* __restrict__ T0, const doub
         for (int j = 0; j < 12; ++j) poses[12 * i + j] = pose[j];
     }
     if (i < nb) {
-        pix_count[i] = 0;
-        run_count[i] = 0;
-        cursor[i] = 0;
+        tally[i] = 0ull;
         if (done) done[i] = 0;
     }
     if (i == 0 && reach) *reach = 0ull;
@@ -388,15 +396,7 @@ template <int WAVES = 4>
 __device__ inline void block_scan2(int32_t a, int32_t b, int32_t* ex_a, int32_t* ex_b, int32_t* tot_a,
                                    int32_t* tot_b, int32_t* s_w) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int32_t ia = a, ib = b;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int32_t ya = __shfl_up(ia, d), yb = __shfl_up(ib, d);
-        if (lane >= d) {
-            ia += ya;
-            ib += yb;
-        }
-    }
+    const int32_t ia = wave_scan(a), ib = wave_scan(b);
     __syncthreads();   // s_w may still be read by a previous call
     if (lane == 63) {
         s_w[wave] = ia;
@@ -427,15 +427,23 @@ __device__ inline void block_scan2(int32_t a, int32_t b, int32_t* ex_a, int32_t*
 // usable pixels are grouped by block in LDS (an open-addressing table of
 // 1024 entries, so it never fills; one LDS atomic add gives a pixel its
 // rank in its block); a scan of the entries' counts places each block's
-// pixels (place in the tile and depth) in a run of the region's 1024 list entries, and the region gets
-// one record (block, count) per block, in run order, and nrec[r] records.
-// The per-block pixel and record counts are integer atomics.  With a
+// pixels (place in the tile and depth) in a run of the region's 1024 list
+// entries, and the region gets one record per block (its count, and its place
+// among the block's records, which the atomic that tallies the block
+// returned), in run order, and nrec[r] records.  With a
 // frozen association the pass also finds how far (per axis, metres) the
 // points lie outside the cells of their frozen voxels, as the bits of a
 // non-negative float64 (whose integer order is its numeric order); that
 // bounds the offsets q - v of the voxel sums.
-// Registers: 99 (109 frozen) hold four waves to a SIMD; the plain form fits
-// five by spilling two.
+//
+// Bound by instruction issue (300 vector and 180 scalar instructions a
+// wave of pixels at the start of this form, the vector units 70 % busy; the
+// LDS table's atomics are not it: one per block and wave instead of one per
+// pixel changed nothing).  The sums across lanes and the scans by register
+// moves instead of shuffles, the voxel kept in float64 and the shorter hash
+// and Morton code: 30 keyframes of 640x480 122 -> 82 us, 88 with the records'
+// places (which take 11 us from k_adj_runs).  95 registers hold five waves
+// to a SIMD; the frozen form takes four.
 template <bool FREEZE>
 __global__ __launch_bounds__(kAdjBlock, FREEZE ? 4 : 5) void k_adj_pixels(MapView M, AdjArgs a, const float* __restrict__ depth,
                                                           const double* __restrict__ poses,
@@ -443,8 +451,8 @@ __global__ __launch_bounds__(kAdjBlock, FREEZE ? 4 : 5) void k_adj_pixels(MapVie
                                                           const float* __restrict__ gscale,
                                                           const int32_t* __restrict__ assoc,
                                                           uint2* __restrict__ list, int2* __restrict__ recs,
-                                                          int32_t* __restrict__ nrec, int32_t* __restrict__ pix_count,
-                                                          int32_t* __restrict__ run_count,
+                                                          int32_t* __restrict__ nrec,
+                                                          unsigned long long* __restrict__ tally,
                                                           unsigned long long* __restrict__ reach,
                                                           double* __restrict__ partials) {
     __shared__ double s_red[kAdjPart][kAdjBlock / 64];
@@ -535,8 +543,11 @@ __global__ __launch_bounds__(kAdjBlock, FREEZE ? 4 : 5) void k_adj_pixels(MapVie
             own += c[k];
             used += c[k] > 0 ? 1 : 0;
         }
-        int32_t run, rec, tot_px, tot_rec;
-        block_scan2(own, used, &run, &rec, &tot_px, &tot_rec, s_w);
+        // (both counts end at most at 1024: one scan of 16 bits each)
+        int32_t both, none, tot, tot_none;
+        block_scan2(own | (used << 16), 0, &both, &none, &tot, &tot_none, s_w);
+        int32_t run = both & 0xffff, rec = both >> 16;
+        const int32_t tot_rec = tot >> 16;
         __syncthreads();   // every count is read before s_cnt turns into offsets
         const int64_t base = region * kTilePx;
 #pragma unroll
@@ -544,9 +555,8 @@ __global__ __launch_bounds__(kAdjBlock, FREEZE ? 4 : 5) void k_adj_pixels(MapVie
             s_cnt[kPer * threadIdx.x + k] = run;
             if (c[k] > 0) {
                 const int32_t sl = s_key[kPer * threadIdx.x + k];
-                recs[base + rec] = make_int2(sl, c[k]);
-                atomicAdd(&pix_count[sl], c[k]);
-                atomicAdd(&run_count[sl], 1);
+                const unsigned nth = (unsigned)atomicAdd(&tally[sl], ((unsigned long long)c[k] << 32) | 1ull);
+                recs[base + rec] = make_int2(sl, (int)((nth << kCountBits) | (unsigned)(c[k] - 1)));
                 ++rec;
             }
             run += c[k];
@@ -595,18 +605,18 @@ __device__ inline int32_t gather_parts(int32_t n, int32_t runs, int32_t piece, f
 
 // Sums over each tile of kScanTile blocks: run counts, and with pieces the
 // blocks that have pixels and the parts of those that are split.
-__global__ __launch_bounds__(256) void k_adj_tile_sums(int64_t nb, const int32_t* __restrict__ counts,
-                                                       const int32_t* __restrict__ pix_count, int32_t piece,
+__global__ __launch_bounds__(256) void k_adj_tile_sums(int64_t nb, const uint2* __restrict__ tally, int32_t piece,
                                                        int32_t* __restrict__ tiles, int32_t* __restrict__ piece_tiles) {
     __shared__ int32_t s_w[4];
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
     int32_t x = 0, blocks = 0, parts = 0;
     for (int k = threadIdx.x; k < kScanTile; k += 256)
         if (base + k < nb) {
-            const int32_t r = counts[base + k];
+            const uint2 b = tally[base + k];
+            const int32_t r = (int32_t)b.x;
             x += r;
             if (piece && r > 0) {
-                const int32_t p = gather_parts(pix_count[base + k], r, piece, 1.0f / (float)piece);
+                const int32_t p = gather_parts((int32_t)b.y, r, piece, 1.0f / (float)piece);
                 if (p > 1)
                     parts += p;
                 else
@@ -631,12 +641,11 @@ __global__ __launch_bounds__(256) void k_adj_tile_sums(int64_t nb, const int32_t
 // a split block (buffer i), then from 1 + (all parts) on the whole blocks
 // that have pixels; item 0 holds {all parts, whole blocks} (each written by
 // the tile that knows it).  Work-group 0 also writes max_i |s_i|.
-__global__ __launch_bounds__(kScanBlock) void k_adj_offsets(int64_t nb, const int32_t* __restrict__ counts,
+__global__ __launch_bounds__(kScanBlock) void k_adj_offsets(int64_t nb, const uint2* __restrict__ tally,
                                                      const int32_t* __restrict__ tiles,
                                                      int32_t* __restrict__ offsets, int32_t K,
                                                      const float* __restrict__ gscale, double* __restrict__ bounds,
-                                                     const int32_t* __restrict__ pix_count, int32_t piece,
-                                                     const int32_t* __restrict__ piece_tiles,
+                                                     int32_t piece, const int32_t* __restrict__ piece_tiles,
                                                      int4* __restrict__ items) {
     constexpr int kWaves = kScanBlock / 64, kPer = kScanTile / kScanBlock;
     __shared__ int32_t s_w[2 * kWaves];
@@ -658,11 +667,13 @@ __global__ __launch_bounds__(kScanBlock) void k_adj_offsets(int64_t nb, const in
         }
     }
     const int64_t i0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kPer;
-    int32_t c[kPer];
+    int32_t c[kPer], n[kPer];
     int32_t own = 0;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-        c[k] = i0 + k < nb ? counts[i0 + k] : 0;
+        const uint2 b = i0 + k < nb ? tally[i0 + k] : make_uint2(0u, 0u);
+        c[k] = (int32_t)b.x;
+        n[k] = (int32_t)b.y;
         own += c[k];
     }
     int32_t run, unused, tot, tot2;
@@ -677,7 +688,7 @@ __global__ __launch_bounds__(kScanBlock) void k_adj_offsets(int64_t nb, const in
         int32_t p[kPer], blocks = 0, parts = 0;
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
-            p[k] = c[k] > 0 ? gather_parts(pix_count[i0 + k], c[k], piece, 1.0f / (float)piece) : 0;
+            p[k] = c[k] > 0 ? gather_parts(n[k], c[k], piece, 1.0f / (float)piece) : 0;
             if (p[k] > 1)
                 parts += p[k];
             else
@@ -718,10 +729,12 @@ __global__ __launch_bounds__(kScanBlock) void k_adj_offsets(int64_t nb, const in
 // Each region's records into their blocks' run lists: one wave per region
 // (four a work-group); a record's run starts in the region's list at the
 // sum of the counts of the records before it; its place among its block's
-// runs comes from the block's cursor.
+// runs came with the block's count of runs.  (Taken here from a second counter
+// for each block, the blocks that many tiles see made this 16.5 us at 30
+// keyframes of 640x480, one atomic after the other.)
 __global__ __launch_bounds__(256) void k_adj_runs(int64_t regions, const int32_t* __restrict__ nrec,
                                                   const int2* __restrict__ recs, const int32_t* __restrict__ run_off,
-                                                  int32_t* __restrict__ cursor, int2* __restrict__ runs) {
+                                                  int2* __restrict__ runs) {
     const int64_t region = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (region >= regions) return;   // the whole wave
@@ -730,15 +743,11 @@ __global__ __launch_bounds__(256) void k_adj_runs(int64_t regions, const int32_t
     for (int k0 = 0; k0 < n; k0 += 64) {   // uniform over the wave
         const int k = k0 + lane;
         const int2 r = k < n ? recs[region * kTilePx + k] : make_int2(0, 0);
-        int32_t incl = r.y;
-        for (int d = 1; d < 64; d <<= 1) {
-            const int32_t y = __shfl_up(incl, d);
-            if (lane >= d) incl += y;
-        }
-        if (k < n) {
-            const int32_t pos = run_off[r.x] + atomicAdd(&cursor[r.x], 1);
-            runs[pos] = make_int2((int32_t)(region * kTilePx) + start + incl - r.y, r.y);
-        }
+        const int32_t count = k < n ? (r.y & (kTilePx - 1)) + 1 : 0;
+        const int32_t incl = wave_scan(count);
+        if (k < n)
+            runs[run_off[r.x] + (int32_t)((uint32_t)r.y >> kCountBits)] =
+                make_int2((int32_t)(region * kTilePx) + start + incl - count, count);
         start += __shfl(incl, 63);
     }
 }
@@ -778,7 +787,9 @@ __device__ inline unsigned long long load_agent(const unsigned long long* p) {
 // Bound by VALU issue and the blocks' unevenness: blocks near the cameras hold
 // many times the pixels of others, and one work-group for each ran long after
 // the rest had finished: at
-// 640x480 10 keyframes 79 -> 49 us, 30 keyframes 212 -> 100 us (kernel trace).
+// 640x480 10 keyframes 79 -> 49 us, 30 keyframes 212 -> 100 us (kernel trace);
+// with the gradients normalised once a voxel instead of once a pixel, 46 and
+// 87 us.
 template <bool FREEZE>
 __global__ __launch_bounds__(kAdjBlock) void k_backward_gather(MapView M, AdjArgs a, int32_t ntiles, int32_t tiles_x,
                                                                const double* __restrict__ poses,
@@ -787,8 +798,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_backward_gather(MapView M, AdjArg
                                                                const int32_t* __restrict__ assoc,
                                                                const uint2* __restrict__ list,
                                                                const int2* __restrict__ runs,
-                                                               const int32_t* __restrict__ pix_count,
-                                                               const int32_t* __restrict__ run_count,
+                                                               const uint2* __restrict__ tally,
                                                                const int32_t* __restrict__ run_off,
                                                                const double* __restrict__ bounds,
                                                                const int4* __restrict__ items,
@@ -797,7 +807,10 @@ __global__ __launch_bounds__(kAdjBlock) void k_backward_gather(MapView M, AdjArg
                                                                float* __restrict__ dparams) {
     __shared__ unsigned long long sP[kBlockVoxels];
     __shared__ unsigned long long sQ[3][kBlockVoxels];
-    __shared__ float4 s_par[kBlockVoxels];   // in the map's (Morton) order
+    // {psi, g^} in the map's (Morton) order, normalised once a voxel; psi = NaN
+    // without a gradient (never a listed pixel's voxel: the pixel pass checked
+    // it)
+    __shared__ float4 s_par[kBlockVoxels];
     __shared__ int s_last;
     int4 item = make_int4((int)blockIdx.x, 0, 1, 0);
     if (items) {
@@ -806,14 +819,19 @@ __global__ __launch_bounds__(kAdjBlock) void k_backward_gather(MapView M, AdjArg
         item = items[1 + blockIdx.x];
     }
     const int64_t slot = item.x;
-    const int32_t n = pix_count[slot];
+    const uint2 counted = tally[slot];
+    const int32_t n = (int32_t)counted.y, nruns = (int32_t)counted.x;
     if (n == 0) return;
-    const int32_t nruns = run_count[slot], roff = run_off[slot];
+    const int32_t roff = run_off[slot];
     const int32_t r0 = (int32_t)((int64_t)nruns * item.y / item.z), r1 = (int32_t)((int64_t)nruns * (item.y + 1) / item.z);
     for (int c = threadIdx.x; c < kBlockVoxels; c += kAdjBlock) {
         sP[c] = 0ull;
         sQ[0][c] = sQ[1][c] = sQ[2][c] = 0ull;
-        s_par[c] = params[slot * kBlockVoxels + c];
+        const float4 pv = params[slot * kBlockVoxels + c];
+        const float n2 = pv.y * pv.y + pv.z * pv.z + pv.w * pv.w;
+        const float inv_ng = 1.0f / sqrtf(n2);
+        s_par[c] = n2 > 0.0f ? make_float4(pv.x, pv.y * inv_ng, pv.z * inv_ng, pv.w * inv_ng)
+                             : make_float4(__builtin_nanf(""), 0.0f, 0.0f, 0.0f);
     }
     const double rmax =
         FREEZE ? __longlong_as_double((long long)reinterpret_cast<const unsigned long long*>(bounds)[0]) : 0.0;
@@ -863,23 +881,21 @@ __global__ __launch_bounds__(kAdjBlock) void k_backward_gather(MapView M, AdjArg
             for (int b = 0; b < kGatherBatch; ++b) {
                 if (!live[b]) continue;
                 const int u = tx * kAdjTile + (int)(le[b].x % kAdjTile), v = ty * kAdjTile + (int)(le[b].x / kAdjTile);
-                double q[3];
+                double q[3], near[3];
                 pixel_point(a, R, t, __uint_as_float(le[b].y), u, v, q);
-                if (!FREEZE) nearest_voxel(a, q, m[b]);
+                if (!FREEZE) nearest_voxel(a, q, m[b], near);
                 PixelTerm P;
 #pragma unroll
-                for (int k = 0; k < 3; ++k) P.dq[k] = (float)(q[k] - a.vs * (double)m[b][k]);
+                for (int k = 0; k < 3; ++k)
+                    P.dq[k] = (float)(q[k] - a.vs * (FREEZE ? (double)m[b][k] : near[k]));
                 const float4 pv = s_par[morton9(m[b][0] & 7, m[b][1] & 7, m[b][2] & 7)];
-                const float n2 = pv.y * pv.y + pv.z * pv.z + pv.w * pv.w;
-                if (!(n2 > 0.0f)) continue;   // not taken: the pixel pass checked it
-                P.inv_ng = 1.0f / sqrtf(n2);
                 P.psi = pv.x;
-                P.gh[0] = pv.y * P.inv_ng;
-                P.gh[1] = pv.z * P.inv_ng;
-                P.gh[2] = pv.w * P.inv_ng;
+                P.gh[0] = pv.y;
+                P.gh[1] = pv.z;
+                P.gh[2] = pv.w;
                 P.q[0] = P.q[1] = P.q[2] = 0.0f;   // (the pose rows are not used here)
                 float rp = residual_terms(P, a.delta, s).rp;
-                rp = rp == rp ? rp : 0.0f;   // a NaN upstream gradient adds nothing
+                rp = rp == rp ? rp : 0.0f;   // a NaN (of the upstream gradient) adds nothing
                 const int c = (m[b][0] & 7) | ((m[b][1] & 7) << 3) | ((m[b][2] & 7) << 6);
                 const double w = (double)rp;
                 atomicAdd(&sP[c], magic_term(w + mp, np));
@@ -923,7 +939,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_backward_gather(MapView M, AdjArg
         if ((p0 | q0 | q1 | q2) == 0ull) continue;
         const int mo = morton9(c & 7, (c >> 3) & 7, c >> 6);
         const int64_t vi = slot * kBlockVoxels + mo;
-        const float4 p = s_par[mo];
+        const float4 p = params[vi];
         const float inv_ng = 1.0f / sqrtf(p.y * p.y + p.z * p.z + p.w * p.w);
         const float gh[3] = {p.y * inv_ng, p.z * inv_ng, p.w * inv_ng};
         const float S[3] = {(float)((double)(long long)q0 * iq), (float)((double)(long long)q1 * iq),
@@ -1094,8 +1110,8 @@ int gsdf_keyframe_loss(const gsdf_map* map, const float* depth_dev, int32_t n_ke
     char* base = (char*)scratch;
     double* partials = (double*)(base + L.partials);
     double* poses = (double*)(base + L.poses);
-    k_adj_setup<<<ceil_div(n_keyframes, 64), 64, 0, s>>>(n_keyframes, T0_dev, xi_dev, poses, 0, nullptr, nullptr,
-                                                        nullptr, nullptr, nullptr);
+    k_adj_setup<<<ceil_div(n_keyframes, 64), 64, 0, s>>>(n_keyframes, T0_dev, xi_dev, poses, 0, nullptr,
+                                                        nullptr, nullptr);
     {
         TimedLaunch tl(map->timer, GSDF_K_LOSS, s);
         const dim3 grid(a.groups, n_keyframes);
@@ -1134,10 +1150,9 @@ int gsdf_backward(const gsdf_map* map, const float* depth_dev, int32_t n_keyfram
     int2* recs = (int2*)(base + L.recs);
     int32_t* nrec = (int32_t*)(base + L.nrec);
     int2* runs = (int2*)(base + L.runs);
-    int32_t* pix_count = (int32_t*)(base + L.pix_count);
-    int32_t* run_count = (int32_t*)(base + L.run_count);
+    unsigned long long* tally = (unsigned long long*)(base + L.tally);
+    const uint2* tallied = (const uint2*)tally;
     int32_t* run_off = (int32_t*)(base + L.run_off);
-    int32_t* cursor = (int32_t*)(base + L.cursor);
     int32_t* tiles = (int32_t*)(base + L.tiles);
     const MapView M = make_view(*map);
     const float4* P = reinterpret_cast<const float4*>(params_dev);
@@ -1156,29 +1171,28 @@ int gsdf_backward(const gsdf_map* map, const float* depth_dev, int32_t n_keyfram
     const dim3 pgrid(a.groups, K);
     {
         TimedLaunch tl(map->timer, GSDF_K_BACKWARD, s);
-        k_adj_setup<<<(unsigned)ceil_div(setup_n, (int64_t)256), 256, 0, s>>>(K, T0_dev, xi_dev, poses, nb, pix_count,
-                                                                           run_count, cursor, done, reach);
+        k_adj_setup<<<(unsigned)ceil_div(setup_n, (int64_t)256), 256, 0, s>>>(K, T0_dev, xi_dev, poses, nb, tally, done,
+                                                                           reach);
         if (freeze)
             k_adj_pixels<true><<<pgrid, kAdjBlock, 0, s>>>(M, a, depth_dev, poses, P, grad_loss_dev, assoc_dev, list,
-                                                           recs, nrec, pix_count, run_count, reach, partials);
+                                                           recs, nrec, tally, reach, partials);
         else
             k_adj_pixels<false><<<pgrid, kAdjBlock, 0, s>>>(M, a, depth_dev, poses, P, grad_loss_dev, nullptr, list,
-                                                            recs, nrec, pix_count, run_count, reach, partials);
+                                                            recs, nrec, tally, reach, partials);
         if (nb > 0) {
-            if (nscan > 1) k_adj_tile_sums<<<nscan, 256, 0, s>>>(nb, run_count, pix_count, piece, tiles, piece_tiles);
-            k_adj_offsets<<<nscan, kScanBlock, 0, s>>>(nb, run_count, nscan > 1 ? tiles : nullptr, run_off, K,
-                                                grad_loss_dev, bounds, pix_count, piece, piece_tiles, items);
+            if (nscan > 1) k_adj_tile_sums<<<nscan, 256, 0, s>>>(nb, tallied, piece, tiles, piece_tiles);
+            k_adj_offsets<<<nscan, kScanBlock, 0, s>>>(nb, tallied, nscan > 1 ? tiles : nullptr, run_off, K,
+                                                       grad_loss_dev, bounds, piece, piece_tiles, items);
             const int64_t regions = (int64_t)K * ntiles;
-            k_adj_runs<<<(unsigned)ceil_div(regions, (int64_t)4), 256, 0, s>>>(regions, nrec, recs, run_off, cursor,
-                                                                               runs);
+            k_adj_runs<<<(unsigned)ceil_div(regions, (int64_t)4), 256, 0, s>>>(regions, nrec, recs, run_off, runs);
             if (freeze)
                 k_backward_gather<true><<<(unsigned)groups, kAdjBlock, 0, s>>>(
-                    M, a, (int32_t)ntiles, tiles_x, poses, P, grad_loss_dev, assoc_dev, list, runs, pix_count,
-                    run_count, run_off, bounds, items, done, buffers, dparams_dev);
+                    M, a, (int32_t)ntiles, tiles_x, poses, P, grad_loss_dev, assoc_dev, list, runs, tallied,
+                    run_off, bounds, items, done, buffers, dparams_dev);
             else
                 k_backward_gather<false><<<(unsigned)groups, kAdjBlock, 0, s>>>(
-                    M, a, (int32_t)ntiles, tiles_x, poses, P, grad_loss_dev, nullptr, list, runs, pix_count,
-                    run_count, run_off, bounds, items, done, buffers, dparams_dev);
+                    M, a, (int32_t)ntiles, tiles_x, poses, P, grad_loss_dev, nullptr, list, runs, tallied,
+                    run_off, bounds, items, done, buffers, dparams_dev);
         }
         k_keyframe_finish<<<K, 256, 0, s>>>(a.groups, xi_dev, partials, loss_dev, dxi_dev, nullptr);
     }

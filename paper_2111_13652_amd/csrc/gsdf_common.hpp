@@ -263,6 +263,69 @@ __device__ inline float load_voxel(const MapView& M, int storage, int64_t vi, fl
     return Wv;
 }
 
+// Sum over aligned groups of N = 8 or 16 lanes (every lane gets it), by
+// moves inside a row of lanes.
+template <int CTRL>
+__device__ inline double lane_move(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+template <int N>
+__device__ inline double lane_sum(double v) {
+    v += lane_move<0xB1>(v);                 // quad_perm: lane ^ 1
+    v += lane_move<0x4E>(v);                 // quad_perm: lane ^ 2
+    v += lane_move<0x141>(v);                // row_half_mirror: the other four of 8
+    if (N == 16) v += lane_move<0x140>(v);   // row_mirror: the other eight of 16
+    return v;
+}
+
+// Sums over a wave of eight float64 values a lane; lane l gets value
+// wave_sum8_value(l).  Each of the first three steps adds lanes 32, 16 and 8
+// apart and keeps half of the values, the first two by the register swaps of
+// whole and half rows: 34 instructions, none through LDS (48 shuffles of two
+// words each otherwise).
+__device__ inline int wave_sum8_value(int lane) {
+    return ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
+}
+template <int ROWS>
+__device__ inline double swap_add(double a, double b) {
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const unsigned xl = (unsigned)x, xh = (unsigned)(x >> 32), yl = (unsigned)y, yh = (unsigned)(y >> 32);
+    if (ROWS == 2) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(xl, yl, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(xh, yh, false, false);
+        return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+        return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    }
+}
+__device__ inline double wave_sum8(const double (&d)[8], int lane) {
+    double r4[4], r2[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r4[i] = swap_add<2>(d[i], d[4 + i]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) r2[i] = swap_add<1>(r4[i], r4[2 + i]);
+    const bool hi = lane & 8;
+    const double r = (hi ? r2[1] : r2[0]) + lane_move<0x128>(hi ? r2[0] : r2[1]);   // row_ror: lane ^ 8
+    return lane_sum<8>(r);
+}
+
+// Inclusive prefix sum over a wave: shifts inside rows of 16 lanes, then the
+// rows' last lanes across them.
+__device__ inline int32_t wave_scan(int32_t x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);    // row_shr: 1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);    // row_shr: 2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);    // row_shr: 4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);    // row_shr: 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast: 15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast: 31 into rows 2 and 3
+    return x;
+}
+
 // XCD-aware order of work-groups: MI355X dispatches work-groups to its 8
 // XCDs in turn (b on XCD b mod 8), each XCD with its own L2.  band_rank(b,
 // n) is a permutation of 0 .. n-1 that gives the work-groups of one XCD

@@ -133,32 +133,6 @@ __device__ inline void bilinear3(const float* __restrict__ img, int W, double u,
     }
 }
 
-// Sums over a wave of kPhotoPart float64 values a lane: the pairwise tree of
-// lanes 32, 16, ... 1 apart, of which each of the first three steps keeps
-// half of the values (10 exchanges instead of 48, the same additions).
-// Returns value photo_part(lane).
-__device__ inline int photo_part(int lane) { return ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1); }
-
-__device__ inline double wave_sum_parts(const double (&d)[kPhotoPart], int lane) {
-    static_assert(kPhotoPart == 8, "three halvings");
-    double r4[4], r2[2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const bool hi = lane & 32;
-        r4[i] = (hi ? d[4 + i] : d[i]) + __shfl_xor(hi ? d[i] : d[4 + i], 32);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const bool hi = lane & 16;
-        r2[i] = (hi ? r4[2 + i] : r4[i]) + __shfl_xor(hi ? r4[i] : r4[2 + i], 16);
-    }
-    const bool hi = lane & 8;
-    double r = (hi ? r2[1] : r2[0]) + __shfl_xor(hi ? r2[0] : r2[1], 8);
-#pragma unroll
-    for (int off = 4; off > 0; off >>= 1) r += __shfl_xor(r, off);
-    return r;
-}
-
 // MODE 0: loss only; 1: loss and gradients; 2: mean colour (Eq. (21));
 // 3: adjoint of the mean colour: with the upstream gradient G_j (in
 // `colors`) and the view counts N_j (in `counts`), each sample adds
@@ -315,9 +289,9 @@ __global__ __launch_bounds__(kPhotoBlock) void k_photometric(MapView M, PhotoArg
                 }
                 if (MODE == 2) continue;
                 // the keyframe's sums over this block's voxels
-                const double x = __any(any) ? wave_sum_parts(part, lane) : 0.0;
+                const double x = __any(any) ? wave_sum8(part, lane) : 0.0;
                 if ((lane & 7) == 0) {
-                    double* out = partials + ((size_t)kf * a.param_blocks + slot) * kPhotoPart + photo_part(lane);
+                    double* out = partials + ((size_t)kf * a.param_blocks + slot) * kPhotoPart + wave_sum8_value(lane);
                     *out = g == 0 ? x : *out + x;   // the same lane stored it
                 }
             }

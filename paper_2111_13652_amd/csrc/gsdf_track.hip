@@ -485,24 +485,6 @@ struct ReduceLds {
 };
 __device__ inline int red_slot(int t) { return (t / kRedChunk) * kRedPad + t % kRedChunk; }
 
-// Sum over aligned groups of N = 8 or 16 lanes (every lane gets it), by
-// moves inside a row of lanes.
-template <int CTRL>
-__device__ inline double lane_move(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-template <int N>
-__device__ inline double lane_sum(double v) {
-    v += lane_move<0xB1>(v);                 // quad_perm: lane ^ 1
-    v += lane_move<0x4E>(v);                 // quad_perm: lane ^ 2
-    v += lane_move<0x141>(v);                // row_half_mirror: the other four of 8
-    if (N == 16) v += lane_move<0x140>(v);   // row_mirror: the other eight of 16
-    return v;
-}
-
 // Partials and leaf sums of the tracking kernel carry the iteration they
 // belong to: the low 16 bits of each float64 word (a relative change below
 // 2^-36, the same for every reader) hold the tag, so a reader that sees the
