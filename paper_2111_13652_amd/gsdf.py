@@ -22,12 +22,17 @@ STORAGE = {"fp32": _lib.FP32, "bf16": _lib.BF16, "fp16": _lib.FP16, "nograd": _l
 COS_75 = math.cos(math.radians(75.0))
 
 
-def _stream() -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+# A call of a few small kernels is bound by the host: what is on its path is
+# kept short.  The current stream's handle comes from the binding that
+# torch.cuda.current_stream wraps in device and stream objects (5 us a call;
+# this 0.4), and addresses are passed as integers (every entry point declares
+# its argument types).
+def _stream() -> int:
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
 def camera(cam) -> _lib.Camera:
@@ -506,8 +511,7 @@ def mean_color(gmap: GsdfMap, params: torch.Tensor, xi: torch.Tensor, depth: tor
     col = torch.empty((n, 512, 3), dtype=torch.float32, device=depth.device)
     cnt = torch.empty((n, 512), dtype=torch.float32, device=depth.device)
     _lib.check(_lib.load().gsdf_mean_color(C.byref(gmap._map), _ptr(depth), _ptr(rgb), K, C.byref(c), _ptr(T0),
-                                            _ptr(xi.detach().contiguous()), _ptr(params.detach().contiguous()), n,
-                                            _ptr(col), _ptr(cnt), _ptr(scratch), scratch.numel(), _stream()),
+                                            _ptr(xi), _ptr(params), n, _ptr(col), _ptr(cnt), _ptr(scratch), scratch.numel(), _stream()),
                "mean_color")
     return col, cnt
 
@@ -576,9 +580,9 @@ class MeanColor(torch.autograd.Function):
         dparams = torch.zeros_like(params)
         dxi = torch.empty_like(xi)
         _lib.check(_lib.load().gsdf_mean_color_backward(
-            C.byref(gmap._map), _ptr(depth), _ptr(rgb), K, C.byref(c), _ptr(T0), _ptr(xi.detach().contiguous()),
-            _ptr(params.detach().contiguous()), int(params.shape[0]), _ptr(g), _ptr(cnt), _ptr(dparams), _ptr(dxi),
-            _ptr(scratch), scratch.numel(), _stream()), "mean_color_backward")
+            C.byref(gmap._map), _ptr(depth), _ptr(rgb), K, C.byref(c), _ptr(T0), _ptr(xi), _ptr(params),
+            int(params.shape[0]), _ptr(g), _ptr(cnt), _ptr(dparams), _ptr(dxi), _ptr(scratch), scratch.numel(),
+            _stream()), "mean_color_backward")
         return (dparams if ctx.needs_input_grad[0] else None, dxi if ctx.needs_input_grad[1] else None,
                 None, None, None, None, None)
 
