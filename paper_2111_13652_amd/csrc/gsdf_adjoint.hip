@@ -37,6 +37,7 @@
 
 #include "gsdf.h"
 #include "gsdf_common.hpp"
+#include "gsdf_finish.hpp"
 #include "gsdf_fixed.hpp"
 #include "gsdf_host.hpp"
 #include "gsdf_se3.hpp"
@@ -954,46 +955,6 @@ __global__ __launch_bounds__(kAdjBlock) void k_backward_gather(MapView M, AdjArg
     }
 }
 
-// One work-group per keyframe: fixed-order sum of `groups` partials (256
-// threads stride over the work-groups, then a tree in LDS), then
-// loss_out[kf] and (when asked) dxi = Jl(xi)^T (pose sums).
-__global__ __launch_bounds__(256) void k_keyframe_finish(int32_t groups, const double* __restrict__ xi,
-                                                         const double* __restrict__ partials,
-                                                         double* __restrict__ loss_out, double* __restrict__ dxi_out,
-                                                         double* __restrict__ count_out) {
-    __shared__ double s_part[kAdjPart][256];
-    const int kf = blockIdx.x;
-    double x[kAdjPart];
-#pragma unroll
-    for (int k = 0; k < kAdjPart; ++k) x[k] = 0.0;
-    for (int g = threadIdx.x; g < groups; g += 256) {
-        const double* p = partials + ((size_t)kf * groups + g) * kAdjPart;
-#pragma unroll
-        for (int k = 0; k < kAdjPart; ++k) x[k] += p[k];
-    }
-#pragma unroll
-    for (int k = 0; k < kAdjPart; ++k) s_part[k][threadIdx.x] = x[k];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w)
-#pragma unroll
-            for (int k = 0; k < kAdjPart; ++k) s_part[k][threadIdx.x] += s_part[k][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x != 0) return;
-    if (loss_out) loss_out[kf] = s_part[0][0];
-    if (count_out) count_out[kf] = s_part[7][0];
-    if (dxi_out) {
-        double Jl[36];
-        se3_left_jacobian(xi + 6 * kf, Jl);
-        for (int c = 0; c < 6; ++c) {
-            double v = 0.0;
-            for (int r = 0; r < 6; ++r) v += Jl[6 * r + c] * s_part[1 + r][0];
-            dxi_out[6 * kf + c] = v;
-        }
-    }
-}
-
 __global__ void k_export_params(MapView M, int storage, int64_t rows, float4* __restrict__ out) {
     const int32_t nb = M.counters[kNumBlocks] < M.max_blocks ? M.counters[kNumBlocks] : M.max_blocks;
     const int64_t n = (rows < (int64_t)nb ? rows : (int64_t)nb) * kBlockVoxels;
@@ -1123,7 +1084,7 @@ int gsdf_keyframe_loss(const gsdf_map* map, const float* depth_dev, int32_t n_ke
             k_keyframe_loss<false><<<grid, kAdjBlock, 0, s>>>(make_view(*map), a, depth_dev, poses, P, assoc_dev,
                                                               partials);
     }
-    k_keyframe_finish<<<n_keyframes, 256, 0, s>>>(a.groups, xi_dev, partials, loss_dev, nullptr, count_dev);
+    k_keyframe_finish<kAdjMaxGroups><<<n_keyframes, kAdjMaxGroups, 0, s>>>(a.groups, xi_dev, partials, loss_dev, nullptr, count_dev);
     return launch_status();
 }
 
@@ -1194,7 +1155,7 @@ int gsdf_backward(const gsdf_map* map, const float* depth_dev, int32_t n_keyfram
                     M, a, (int32_t)ntiles, tiles_x, poses, P, grad_loss_dev, nullptr, list, runs, tallied,
                     run_off, bounds, items, done, buffers, dparams_dev);
         }
-        k_keyframe_finish<<<K, 256, 0, s>>>(a.groups, xi_dev, partials, loss_dev, dxi_dev, nullptr);
+        k_keyframe_finish<kAdjMaxGroups><<<K, kAdjMaxGroups, 0, s>>>(a.groups, xi_dev, partials, loss_dev, dxi_dev, nullptr);
     }
     return launch_status();
 }

@@ -18,7 +18,7 @@
 // take part (those holding the surface: about 5 % on a room map, 64 to 130 in
 // a block that has any), so the work-group first lists them in voxel order.
 // Then its four waves take the keyframes in turn, each with the listed voxels
-// on its lanes (two a lane, 128 together): a keyframe's pose sums stay within
+// on its lanes (64 together): a keyframe's pose sums stay within
 // a wave, which stores them as the block's partial without a barrier, and a
 // voxel's psi and colour gradients are summed in registers and, over the
 // waves, once in LDS before the voxel is written (no atomics).  A second
@@ -30,13 +30,19 @@
 // wants waves in flight.  With the listed voxels spread over the work-group's
 // threads and all of it walking the keyframes together, one or two waves of
 // four worked, with two barriers a keyframe: loss and gradients of 30
-// keyframes at 640x480 took 247 us (kernel trace), now 99.
+// keyframes at 640x480 took 247 us (kernel trace); with the waves on
+// keyframes in turn and two voxels a lane 99, three waves to a SIMD for 162
+// registers; with one voxel a lane (121 registers, four waves) and the far
+// voxels left out before their float64 root, 84.  (Both voxels' loads under
+// way together took 197 registers and 110 us; a bound of five waves spills:
+// 104; work-groups of eight waves: 85, and 29 against 25 for 5 keyframes.)
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
 #include "gsdf.h"
 #include "gsdf_common.hpp"
+#include "gsdf_finish.hpp"
 #include "gsdf_host.hpp"
 #include "gsdf_se3.hpp"
 
@@ -59,7 +65,7 @@ struct PhotoArgs {
 struct PhotoVoxel {
     bool ok;
     double p[3], gh[3];
-    float ghf[3], rho[3];
+    float rho[3];
 };
 
 __device__ inline void photo_voxel(const MapView& M, const PhotoArgs& a, const float4* __restrict__ params,
@@ -68,6 +74,10 @@ __device__ inline void photo_voxel(const MapView& M, const PhotoArgs& a, const f
     const int64_t vi = slot * kBlockVoxels + c;
     if (!(M.weight[vi] > 0.0f)) return;
     const float4 q = params[vi];
+    // |psi gh_k| <= v_s/2 on every axis, as below, needs |psi| <= 0.8661 v_s
+    // (the largest |gh_k| is at least 1/sqrt(3)): most voxels stop here,
+    // before the root and the divisions in float64
+    if (fabs((double)q.x) > 0.875 * a.vs) return;
     const double g0 = q.y, g1 = q.z, g2 = q.w;
     const double ng = sqrt(g0 * g0 + g1 * g1 + g2 * g2);
     if (!(ng > 0.0)) return;
@@ -85,7 +95,6 @@ __device__ inline void photo_voxel(const MapView& M, const PhotoArgs& a, const f
     const int m[3] = {8 * bx + lx, 8 * by + ly, 8 * bz + lz};
     for (int k = 0; k < 3; ++k) {
         V->p[k] = a.vs * (double)m[k] - psi * V->gh[k];
-        V->ghf[k] = (float)V->gh[k];
         V->rho[k] = colors ? colors[3 * vi + k] : 0.0f;
     }
     V->ok = true;
@@ -151,7 +160,7 @@ __global__ __launch_bounds__(kPhotoBlock) void k_photometric(MapView M, PhotoArg
                                                             double* __restrict__ partials) {
     constexpr int kWaves = kPhotoBlock / 64;
     // a batch's terms of each voxel: keyframes x voxels, two batches in turn
-    __shared__ float4 s_term[MODE == 0 ? 1 : 2][MODE == 0 ? 1 : kWaves * kPhotoBatch][MODE == 0 ? 1 : 2 * 64];
+    __shared__ float4 s_term[MODE == 0 ? 1 : 2][MODE == 0 ? 1 : kWaves * kPhotoBatch][MODE == 0 ? 1 : 64];
     __shared__ int s_wcount[2][kWaves];
     __shared__ short s_list[kBlockVoxels];
     const int64_t slot = blockIdx.x;
@@ -197,27 +206,22 @@ __global__ __launch_bounds__(kPhotoBlock) void k_photometric(MapView M, PhotoArg
                 partials[((size_t)(i / kPhotoPart) * a.param_blocks + slot) * kPhotoPart + i % kPhotoPart] = 0.0;
         return;
     }
-    // 2. 128 listed voxels at a time: on every wave, lane l takes l and l + 64
+    // 2. 64 listed voxels at a time, one to a lane of every wave
     const size_t npx = (size_t)a.W * a.H;
-    for (int g = 0; g < n_act; g += 128) {
-        PhotoVoxel V[2];
-        int vc[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int r = g + lane + h * 64;
-            V[h].ok = false;
-            vc[h] = 0;
-            if (r >= n_act) continue;
-            vc[h] = s_list[r];
-            photo_voxel(M, a, params, MODE == 2 ? nullptr : colors, slot, vc[h], &V[h]);
+    for (int g = 0; g < n_act; g += 64) {
+        PhotoVoxel V;
+        V.ok = false;
+        if (g + lane < n_act) {
+            const int c = s_list[g + lane];
+            photo_voxel(M, a, params, MODE == 2 ? nullptr : colors, slot, c, &V);
             if (MODE == 3) {
                 // upstream gradient per sample of the mean: G_j / N_j
-                const float n = counts[slot * kBlockVoxels + vc[h]];
+                const float n = counts[slot * kBlockVoxels + c];
 #pragma unroll
-                for (int c = 0; c < 3; ++c) V[h].rho[c] /= n;
+                for (int c = 0; c < 3; ++c) V.rho[c] /= n;
             }
         }
-        // thread r < 128: sums of listed voxel g + r.  MODE 2: colours and view
+        // thread r < 64: sums of listed voxel g + r.  MODE 2: colours and view
         // count; else colour and psi gradients
         float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         for (int k0 = 0, buf = 0; k0 < a.K; k0 += kWaves * kPhotoBatch, buf ^= 1) {
@@ -229,32 +233,28 @@ __global__ __launch_bounds__(kPhotoBlock) void k_photometric(MapView M, PhotoArg
                 for (int k = 0; k < kPhotoPart; ++k) part[k] = 0.0;
                 const double* T = poses + 12 * kf;
                 const float s = MODE == 1 ? gscale[kf] : 1.0f;
-                bool any = false;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    if (MODE != 0) s_term[buf][j * kWaves + wave][lane + h * 64] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    if (!V[h].ok) continue;
-                    PhotoProj P;
-                    if (!photo_project(a, T, depth + kf * npx, V[h], &P)) continue;
-                    any = true;
-                    float I[3], dIu[3], dIv[3];
-                    bilinear3(rgb + 3 * kf * npx, a.W, P.u, P.v, I, dIu, dIv);
-                    if (MODE == 2) {
-                        s_term[buf][j * kWaves + wave][lane + h * 64] = make_float4(I[0], I[1], I[2], 1.0f);
-                        continue;
-                    }
-                    part[7] += 1.0;
+                PhotoProj P;
+                const bool seen = V.ok && photo_project(a, T, depth + kf * npx, V, &P);
+                if (MODE != 0) s_term[buf][j * kWaves + wave][lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                float I[3], dIu[3], dIv[3];
+                if (seen) bilinear3(rgb + 3 * kf * npx, a.W, P.u, P.v, I, dIu, dIv);
+                if (MODE == 2) {
+                    if (seen) s_term[buf][j * kWaves + wave][lane] = make_float4(I[0], I[1], I[2], 1.0f);
+                    continue;
+                }
+                if (seen) {
+                    part[7] = 1.0;
                     float eu = 0.0f, ev = 0.0f, loss = 0.0f, drho[3] = {0.0f, 0.0f, 0.0f};
                     if (MODE == 3) {
 #pragma unroll
                         for (int c = 0; c < 3; ++c) {
-                            eu += V[h].rho[c] * dIu[c];
-                            ev += V[h].rho[c] * dIv[c];
+                            eu += V.rho[c] * dIu[c];
+                            ev += V.rho[c] * dIv[c];
                         }
                     }
 #pragma unroll
                     for (int c = 0; c < 3 && MODE != 3; ++c) {
-                        const float r = I[c] - V[h].rho[c];
+                        const float r = I[c] - V.rho[c];
                         const float ar = fabsf(r);
                         const bool quad = ar <= a.delta;
                         loss += a.lambda * (quad ? 0.5f * r * r : a.delta * (ar - 0.5f * a.delta));
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(kPhotoBlock) void k_photometric(MapView M, PhotoArg
                             ev += rp * dIv[c];
                         }
                     }
-                    part[0] += (double)loss;
+                    part[0] = (double)loss;
                     if (MODE == 1 || MODE == 3) {
                         const float iz = (float)P.iz;
                         const float fx = (float)a.fx, fy = (float)a.fy;
@@ -275,21 +275,20 @@ __global__ __launch_bounds__(kPhotoBlock) void k_photometric(MapView M, PhotoArg
 #pragma unroll
                         for (int r = 0; r < 3; ++r)
                             aw[r] = (float)T[4 * r] * gx[0] + (float)T[4 * r + 1] * gx[1] + (float)T[4 * r + 2] * gx[2];
-                        s_term[buf][j * kWaves + wave][lane + h * 64] =
+                        s_term[buf][j * kWaves + wave][lane] =
                             make_float4(drho[0], drho[1], drho[2],
-                                        -(aw[0] * V[h].ghf[0] + aw[1] * V[h].ghf[1] + aw[2] * V[h].ghf[2]));
-                        const float p0 = (float)V[h].p[0], p1 = (float)V[h].p[1], p2 = (float)V[h].p[2];
-                        part[1] -= (double)aw[0];
-                        part[2] -= (double)aw[1];
-                        part[3] -= (double)aw[2];
-                        part[4] += (double)(aw[1] * p2 - aw[2] * p1);
-                        part[5] += (double)(aw[2] * p0 - aw[0] * p2);
-                        part[6] += (double)(aw[0] * p1 - aw[1] * p0);
+                                        -(aw[0] * (float)V.gh[0] + aw[1] * (float)V.gh[1] + aw[2] * (float)V.gh[2]));
+                        const float p0 = (float)V.p[0], p1 = (float)V.p[1], p2 = (float)V.p[2];
+                        part[1] = -(double)aw[0];
+                        part[2] = -(double)aw[1];
+                        part[3] = -(double)aw[2];
+                        part[4] = (double)(aw[1] * p2 - aw[2] * p1);
+                        part[5] = (double)(aw[2] * p0 - aw[0] * p2);
+                        part[6] = (double)(aw[0] * p1 - aw[1] * p0);
                     }
                 }
-                if (MODE == 2) continue;
                 // the keyframe's sums over this block's voxels
-                const double x = __any(any) ? wave_sum8(part, lane) : 0.0;
+                const double x = __any(seen) ? wave_sum8(part, lane) : 0.0;
                 if ((lane & 7) == 0) {
                     double* out = partials + ((size_t)kf * a.param_blocks + slot) * kPhotoPart + wave_sum8_value(lane);
                     *out = g == 0 ? x : *out + x;   // the same lane stored it
@@ -297,7 +296,7 @@ __global__ __launch_bounds__(kPhotoBlock) void k_photometric(MapView M, PhotoArg
             }
             if (MODE == 0) continue;
             __syncthreads();
-            if (threadIdx.x < 128) {
+            if (threadIdx.x < 64) {
 #pragma unroll
                 for (int j = 0; j < kWaves * kPhotoBatch; ++j) {
                     if (k0 + j >= a.K) break;
@@ -310,7 +309,7 @@ __global__ __launch_bounds__(kPhotoBlock) void k_photometric(MapView M, PhotoArg
             }
         }
         const int r = g + threadIdx.x;
-        if (MODE != 0 && threadIdx.x < 128 && r < n_act) {
+        if (MODE != 0 && threadIdx.x < 64 && r < n_act) {
             const int64_t vi = slot * kBlockVoxels + s_list[r];
             if (MODE == 2) {
                 const float n = sum.w;
@@ -328,39 +327,6 @@ __global__ __launch_bounds__(kPhotoBlock) void k_photometric(MapView M, PhotoArg
             }
         }
         __syncthreads();   // the terms are written again for the next voxels
-    }
-}
-
-// One work-group per keyframe: fixed-order sum over the map blocks' partials.
-__global__ __launch_bounds__(256) void k_photometric_finish(PhotoArgs a, const double* __restrict__ xi,
-                                                            const double* __restrict__ partials,
-                                                            double* __restrict__ loss_out,
-                                                            double* __restrict__ count_out,
-                                                            double* __restrict__ dxi_out) {
-    __shared__ double s_part[kPhotoPart][256];
-    const int kf = blockIdx.x;
-    double x[kPhotoPart];
-    for (int k = 0; k < kPhotoPart; ++k) x[k] = 0.0;
-    for (int64_t b = threadIdx.x; b < a.param_blocks; b += 256)
-        for (int k = 0; k < kPhotoPart; ++k) x[k] += partials[((size_t)kf * a.param_blocks + b) * kPhotoPart + k];
-    for (int k = 0; k < kPhotoPart; ++k) s_part[k][threadIdx.x] = x[k];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w)
-            for (int k = 0; k < kPhotoPart; ++k) s_part[k][threadIdx.x] += s_part[k][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x != 0) return;
-    if (loss_out) loss_out[kf] = s_part[0][0];
-    if (count_out) count_out[kf] = s_part[7][0];
-    if (dxi_out) {
-        double Jl[36];
-        se3_left_jacobian(xi + 6 * kf, Jl);
-        for (int c = 0; c < 6; ++c) {
-            double v = 0.0;
-            for (int r = 0; r < 6; ++r) v += Jl[6 * r + c] * s_part[1 + r][0];
-            dxi_out[6 * kf + c] = v;
-        }
     }
 }
 
@@ -459,7 +425,7 @@ static void photo_launch(int mode, const gsdf_map* map, const float* depth, cons
                 M, a, depth, rgb, poses, P, colors, nullptr, dparams, nullptr, nullptr, nullptr, counts, partials);
     }
     if (mode != 2)
-        k_photometric_finish<<<K, 256, 0, s>>>(a, xi, partials, loss_out, count_out, dxi_out);
+        k_keyframe_finish<1024><<<K, 1024, 0, s>>>(a.param_blocks, xi, partials, loss_out, dxi_out, count_out);
 }
 
 // Quadratic regulariser of the distances towards reference values
