@@ -17,7 +17,9 @@
 // that XCD's L2).  Every work-group then reads the leaf sums the same
 // way, adds them in the same fixed order and solves the 6x6 system itself,
 // so all of them hold the bit-identical new pose without a round trip
-// through a publisher; work-group 0 writes the final pose.
+// through a publisher; work-group 0 writes the final pose.  A small level of
+// the plain form has no leaves: the work-groups of one XCD take it, and each
+// adds all of their partials.
 // Waits are bounded spins, so every wave exits even if something went
 // wrong.  Float64 partial sums keep the rounding noise of b far below what a
 // rank-deficient H (a lone sphere) would amplify through the damping.
@@ -738,13 +740,15 @@ __device__ inline bool solve_update_wave(const double* ne, double damping, doubl
 // XCDs without cache maintenance: such a store writes through the writer's
 // L2, such a load does not return a line its L2 holds clean.  One exception
 // keeps a hop inside an XCD: the tracking kernel's partials go to their
-// leaf's first work-group, which runs on the same XCD, and are stored at
+// leaf's first work-group, which runs on the same XCD (on a one-XCD level to
+// the level's other work-groups), and are stored at
 // work-group scope.  That store leaves the line dirty in the XCD's L2, and
 // a device-scope load from the same XCD returns a dirty line of its own L2
 // (measured on MI355X: a store-to-load round trip of 0.46 us between two
 // work-groups on one XCD against 0.85 us with device-scope stores, and
 // 1.2 us between XCDs).  A work-group that does not find itself on its leaf
-// leader's XCD (the leader publishes its hardware XCC id) stores its
+// leader's XCD (the leader publishes its hardware XCC id; on a one-XCD level
+// every work-group does, and all must agree) stores its
 // partials at device scope instead, so the exchange never depends on the
 // dispatch order for its correctness.  A tagged word (the tracking kernel's
 // partials and leaf sums) needs nothing more: it is written by one 64-bit
@@ -1074,7 +1078,9 @@ __device__ inline bool level_member(const LevelPlan& p, int b) {
 // each of those was published after its leaf's members had contributed to
 // gi + 1, which they do only after reading the sums of gi, and by the first
 // work-group of the leaf after it had read the leaf's partials of gi, so no
-// set is read while it is overwritten.  The published pose of a level
+// set is read while it is overwritten.  (On a one-XCD level each member reads
+// every partial of gi before it contributes to gi + 1, and the members go on
+// to every larger level.)  The published pose of a level
 // boundary is overwritten only at the next boundary, which needs the
 // contributions of the work-groups that joined and read it.
 template <int STORAGE, int MODEL>
