@@ -437,6 +437,13 @@ __device__ inline void block_scan2(int32_t a, int32_t b, int32_t* ex_a, int32_t*
 // non-negative float64 (whose integer order is its numeric order); that
 // bounds the offsets q - v of the voxel sums.
 //
+// A pixel without a finite offset is not listed: a fixed-point term of a NaN
+// or an infinity would be an arbitrary integer in the sums of a voxel that
+// other keyframes share.  So a keyframe whose pose is not finite (a NaN twist)
+// lists nothing and reaches nowhere, and its own loss and pose sums alone are
+// NaN.  At a finite pose the nearest voxel lies within half a voxel of the
+// point; only a frozen one can be out of float32's range.
+//
 // Bound by instruction issue (300 vector and 180 scalar instructions a
 // wave of pixels at the start of this form, the vector units 70 % busy; the
 // LDS table's atomics are not it: one per block and wave instead of one per
@@ -473,6 +480,7 @@ __global__ __launch_bounds__(kAdjBlock, FREEZE ? 4 : 5) void k_adj_pixels(MapVie
         t[r] = poses[12 * kf + 4 * r + 3];
     }
     const float s = gscale[kf];
+    const bool finite = pose_finite(poses + 12 * kf);   // uniform over the work-group
     const int N = a.W * a.H;
     const float* dimg = depth + (size_t)kf * N;
     const int32_t* aimg = FREEZE ? assoc + (size_t)kf * N * 3 : nullptr;
@@ -521,6 +529,8 @@ __global__ __launch_bounds__(kAdjBlock, FREEZE ? 4 : 5) void k_adj_pixels(MapVie
 #pragma unroll
                 for (int k = 0; k < 6; ++k) acc[1 + k] += rt.rp * rt.J[k];
                 acc[7] += 1.0f;
+                if (!finite) continue;
+                if (FREEZE && !(isfinite(P[j].dq[0]) && isfinite(P[j].dq[1]) && isfinite(P[j].dq[2]))) continue;
                 // the block's entry in the tile's table (at most 1024 keys: a
                 // free or matching entry is always found)
                 const int32_t sl = slot[j];
@@ -572,7 +582,7 @@ __global__ __launch_bounds__(kAdjBlock, FREEZE ? 4 : 5) void k_adj_pixels(MapVie
     }
     const double x = block_sum_part(acc, s_red);
     if (threadIdx.x < kAdjPart) partials[((size_t)kf * a.groups + grp) * kAdjPart + threadIdx.x] = x;
-    if (!FREEZE) return;
+    if (!FREEZE || !finite) return;
     for (int off = 32; off > 0; off >>= 1) e = fmax(e, __shfl_xor(e, off));
     if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = e;
     __syncthreads();
