@@ -469,7 +469,13 @@ __device__ inline void accumulate_trilinear(const MapView& M, const TrackLevel& 
 // float64 keeps: where a thread holds a single pixel its sums are exact
 // products, and on an ill-conditioned system (a sphere, whose rotations
 // about its centre leave the residuals unchanged) the tracked centre moved
-// 40 times further from the float64 oracle's.  The precision form
+// 40 times further from the float64 oracle's.  A float32 sum of four threads
+// that hold two pixels each spans eight pixels and does the same, so a one-XCD
+// level, whose threads hold two, adds every thread's values in float64 (WIDE;
+// 1.9 us a launch of 19 iterations at 160x120).  The sphere, 160x120, 24
+// starts: rotation after one iteration 5.1e-7 rad rms from the oracle's in
+// fours, 1.7e-7 wide (6.0e-7 in fours of single pixels); centre after ten, in
+// the median, 1.4e-7 m, 6e-9 wide (9e-8).  The precision form
 // (COMP) uses compensated float32 at every stage: 8 threads per entry, two
 // chunks each, then the first kNE threads add the 8 parts.
 //
@@ -513,7 +519,7 @@ __device__ inline void store_entry(double* partial, int k, double s, unsigned lo
         __hip_atomic_store(&partial[k], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <bool COMP>
+template <bool COMP, bool WIDE = false>
 __device__ inline void store_partial(const float acc[kNE], const float cmp[kNE], double* partial,
                                      ReduceLds& r, unsigned long long tag = 0, bool local = false) {
     const int slot = red_slot(threadIdx.x);
@@ -547,7 +553,9 @@ __device__ inline void store_partial(const float acc[kNE], const float cmp[kNE],
             for (int j = 0; j < kRedChunk / 4; ++j) q[j] = src[j];
             double t[kRedChunk / 4];
 #pragma unroll
-            for (int j = 0; j < kRedChunk / 4; ++j) t[j] = (double)((q[j].x + q[j].y) + (q[j].z + q[j].w));
+            for (int j = 0; j < kRedChunk / 4; ++j)
+                t[j] = WIDE ? ((double)q[j].x + (double)q[j].y) + ((double)q[j].z + (double)q[j].w)
+                            : (double)((q[j].x + q[j].y) + (q[j].z + q[j].w));
 #pragma unroll
             for (int w = kRedChunk / 8; w >= 1; w /= 2) {
 #pragma unroll
@@ -1210,7 +1218,7 @@ __global__ __launch_bounds__(kTrackBlock) void k_track_frame(MapView M, TrackArg
             // sums), the same solve
             bool part_ok = true;
             if (plan.one)
-                store_partial<COMP>(acc, cmp, part + (size_t)(b / kXcds) * kPartStride, red, tag, here != 0);
+                store_partial<COMP, true>(acc, cmp, part + (size_t)(b / kXcds) * kPartStride, red, tag, here != 0);
             else
                 part_ok = contribute<COMP>(acc, cmp, part, leafpart, Gl, sync, a.tag_polls, red, tag, here != 0);
             if (stamp) a.clocks[4 * gi + 1] = wall_clock64() - t0;
