@@ -17,6 +17,7 @@ constexpr int kAllocSet = 1024;  // LDS set capacity (keys) per tile
 // and marked as touched by this frame, by about the number of the tile's
 // pixels whose band meets the block (s_px).  Every thread of the 256-thread
 // work-group must call it (it synchronises); red holds 4 words of LDS.
+template <bool ADD_UP>
 __device__ inline void allocate_tile(const MapView& M, const float* __restrict__ depth, int W, int H, float zmin,
                                      float zmax, const BandConsts& bc, const double* __restrict__ Twc,
                                      int32_t* status, int tu, int tv, unsigned long long* s_keys,
@@ -70,7 +71,7 @@ __device__ inline void allocate_tile(const MapView& M, const float* __restrict__
             if (!placed) {  // set full: go to the global table directly
                 int created;
                 const int32_t slot = hash_insert(M, bx, by, bz, status, &created);
-                if (slot >= 0) mark_touched(M, slot, 1);
+                if (slot >= 0) mark_touched<ADD_UP>(M, slot, 1);
             }
         }
     }
@@ -83,7 +84,7 @@ __device__ inline void allocate_tile(const MapView& M, const float* __restrict__
         unpack_key(key, &bx, &by, &bz);
         // the inserting thread marks a new block; others mark known slots
         const int32_t slot = hash_insert(M, bx, by, bz, status, &created);
-        if (slot >= 0) mark_touched(M, slot, max(s_px[i], 1));
+        if (slot >= 0) mark_touched<ADD_UP>(M, slot, max(s_px[i], 1));
         ++probes;
     }
     probes = block_sum_u64(probes, red);

@@ -147,6 +147,7 @@ struct AuxLayout {
 constexpr int kFuseTeams = 8;
 constexpr int kMaxParts = 8;
 constexpr int kTeamBuffers = 256;               // partial-sum buffers of a team's split blocks
+constexpr int kTouchedMost = 1 << 30;           // a count takes no more from there on (see mark_touched)
 __host__ __device__ inline size_t touched_slots(size_t nb) { return (nb + 511) / 512 * 512; }   // whole chunks of every team
 
 enum Counter { kNumBlocks = 0, kTeamTicket = 64, kTeamDone = kTeamTicket + kFuseTeams * 16,
@@ -402,8 +403,13 @@ __device__ inline unsigned long long wave_sum_u64(unsigned long long x) {
 
 // Record that `pixels` more pixels of the current frame touch a block (the
 // fusion kernel that consumes the count runs later): a device-scope atomic
-// without a return, so nothing waits for it.
+// without a return, so nothing waits for it.  The counts end with the fusion
+// that consumes them; allocation alone (ADD_UP) may be called any number of
+// times before one, so it stops adding at kTouchedMost, to which a frame adds
+// less than as much again.
+template <bool ADD_UP>
 __device__ inline void mark_touched(const MapView& M, int32_t slot, int pixels) {
+    if (ADD_UP && M.touched[slot] >= kTouchedMost) return;
     __hip_atomic_fetch_add(&M.touched[slot], pixels, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 

@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256) void k_alloc_normals(MapView M, const float* _
     __shared__ float tile[kTileH][kTileH + 1];
     __shared__ float itile[kTileH][kTileH + 1];
     if (blockIdx.z == 0)
-        allocate_tile(M, depth, fc.W, fc.H, fc.zmin, fc.zmax, fc.band, Twc, status, blockIdx.x, blockIdx.y, s_keys,
+        allocate_tile<false>(M, depth, fc.W, fc.H, fc.zmin, fc.zmax, fc.band, Twc, status, blockIdx.x, blockIdx.y, s_keys,
                       s_px, red);
     else
         normals_tile(depth, fc, Twc, pix, blockIdx.x, blockIdx.y, tile, itile);
@@ -438,6 +438,8 @@ __global__ __launch_bounds__(kFuseBlock, 4) void k_fuse_blocks(MapView M, const 
     for (int i = threadIdx.x; i < kClasses * 65; i += kFuseBlock) (&s_pre[0][0])[i] = 0;
     // pixels to a piece: the share of a member, so that a frame whose blocks
     // are few or uneven still fills the chip
+    // (counts of very many allocations may wrap in the sum: it sizes the
+    // pieces, the result does not depend on it)
     int sum = ahead.x + ahead.y + ahead.z + ahead.w;
 #pragma unroll 1
     for (int j = my_chunk + kPerStep; j < team_chunks; j += kPerStep) {

@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256) void k_allocate(MapView M, const float* __rest
     __shared__ unsigned long long s_keys[kAllocSet];
     __shared__ int s_px[kAllocSet];
     __shared__ unsigned long long red[4];
-    allocate_tile(M, depth, W, H, zmin, zmax, bc, Twc, status, blockIdx.x, blockIdx.y, s_keys, s_px, red);
+    allocate_tile<true>(M, depth, W, H, zmin, zmax, bc, Twc, status, blockIdx.x, blockIdx.y, s_keys, s_px, red);
 }
 
 __global__ void k_sum_stats(MapView M, unsigned long long* out) {
