@@ -105,6 +105,12 @@ struct PhotoProj {
     double x[3], z, iz, u, v;
 };
 
+// n / z with z's reciprocal at hand
+__device__ inline double quotient(double n, double z, double iz) {
+    const double q = n * iz;
+    return fma(fma(-z, q, n), iz, q);
+}
+
 __device__ inline bool photo_project(const PhotoArgs& a, const double* T, const float* __restrict__ depth_i,
                                      const PhotoVoxel& V, PhotoProj* P) {
     const double d[3] = {V.p[0] - T[3], V.p[1] - T[7], V.p[2] - T[11]};
@@ -112,13 +118,16 @@ __device__ inline bool photo_project(const PhotoArgs& a, const double* T, const 
     P->z = P->x[2];
     if (!(P->z >= a.zmin)) return false;
     // one reciprocal (hardware estimate and two Newton steps: within an ulp)
-    // for both quotients and the gradient's 1 / z
+    // for both quotients and the gradient's 1 / z.  The quotients decide
+    // visibility (image border, nearest pixel), so each is corrected by its
+    // exact remainder (Markstein, IBM J. Res. Dev. 34, 1990) to the rounding
+    // of a division: uncorrected, points exactly on column 0 fall outside.
     double iz = __builtin_amdgcn_rcp(P->z);
     iz = fma(iz, fma(-P->z, iz, 1.0), iz);
     iz = fma(iz, fma(-P->z, iz, 1.0), iz);
     P->iz = iz;
-    P->u = fma(a.fx * P->x[0], iz, a.cx);
-    P->v = fma(a.fy * P->x[1], iz, a.cy);
+    P->u = quotient(a.fx * P->x[0], P->z, iz) + a.cx;
+    P->v = quotient(a.fy * P->x[1], P->z, iz) + a.cy;
     if (!(P->u >= 0.0 && P->u < (double)(a.W - 1) && P->v >= 0.0 && P->v < (double)(a.H - 1))) return false;
     const int iu = (int)floor(P->u + 0.5), iv = (int)floor(P->v + 0.5);
     const float D = depth_i[(size_t)iv * a.W + iu];
