@@ -1486,22 +1486,13 @@ constexpr int kMaxGnKeyframes = 65535;
 // and store) are shared by more pixels.  Measured at 30 keyframes of
 // 640x480 with one work-group on a CU: 190 us at 2 pixels a thread, 160 at 4,
 // 138 at 8, 132 at 16 (which leaves most CUs idle below about 8 keyframes).
+// The number goes by the image alone, so that a keyframe's step is the same
+// bits in any batch and on any number of CUs, and a thread's float32 sums stay
+// as short.  (As many work-groups as fill the chip a whole number of times, 68
+// instead of 75 for 30 keyframes of 640x480, take 68.3 us instead of 70.1.)
 inline int gn_groups(int npx) {
     const int g = ceil_div(npx, kTrackBlock * 8);
     return g < 1 ? 1 : (g > kMaxGroups ? kMaxGroups : g);
-}
-
-// The float32 form's work-groups per keyframe, of at most g: where all of
-// them fill the chip (two work-groups a CU), as many as fill it a whole number
-// of times, so that no last, mostly empty turn follows.  Measured at 640x480:
-// 10 keyframes (750 work-groups of 512 at a time, now 510) 33 -> 29 us, 30
-// keyframes (2250, now 2040) 73 -> 70.  The 16-bit forms keep g: their sums'
-// grouping stays.
-inline int gn_whole_turns(int g, int n_keyframes, int resident) {
-    const int64_t turns = resident > 0 ? (int64_t)g * n_keyframes / resident : 0;
-    if (turns < 1) return g;
-    const int64_t even = turns * resident / n_keyframes;
-    return even < 1 ? 1 : (int)(even < g ? even : g);
 }
 
 inline int normal_eq_groups(int npx) {
@@ -1798,8 +1789,7 @@ extern "C" int gsdf_gn_step_keyframes(const gsdf_map* map, const float* depth_de
     a.join_polls = kJoinPolls;
     a.clocks = nullptr;
     a.device_scope = 1;
-    int g = gn_groups(cam->width * cam->height);
-    if (map->desc.storage == GSDF_FP32) g = gn_whole_turns(g, n_keyframes, 2 * track_groups());
+    const int g = gn_groups(cam->width * cam->height);
     const dim3 grid(g, n_keyframes);
     double* partials = (double*)scratch_dev;
     const MapView M = make_view(*map);
