@@ -489,7 +489,11 @@ struct ReduceLds {
     float v[kNE][16 * kRedPad];
     double part[3][kNE][8];   // COMP: of store_partial, and of two sums after it: no barrier between them
     double tot[kNE];
-    int fail;                 // a wait of total_leaves ended without its tag
+    // a wait of the first or second sum after store_partial ended without its
+    // tag: a word each, so that a wave that has gone on to the second sum
+    // changes nothing that a slower one has yet to read of the first, and the
+    // whole work-group leaves at the same place
+    int fail[2];
 };
 __device__ inline int red_slot(int t) { return (t / kRedChunk) * kRedPad + t % kRedChunk; }
 
@@ -946,7 +950,7 @@ __device__ inline bool total_leaves(const double* leafpart, int nleaf, unsigned 
                 if (COMP) ks.add((float)untag_word(x[j])); else s += untag_word(x[j]);
             }
         }
-        if (!ok) r.fail = 1;
+        if (!ok) r.fail[buf - 1] = 1;
         if (COMP) {
             r.part[buf][k][p] = (double)ks.value();
         } else {
@@ -961,7 +965,7 @@ __device__ inline bool total_leaves(const double* leafpart, int nleaf, unsigned 
     }
     if (COMP) {
         __syncthreads();
-        if (r.fail) return false;
+        if (r.fail[0] | (buf == 2 && r.fail[1])) return false;
         if (threadIdx.x < kNE) {
             const int k = threadIdx.x;
             Kahan ks;
@@ -974,7 +978,7 @@ __device__ inline bool total_leaves(const double* leafpart, int nleaf, unsigned 
     }
     if (leaf) return true;
     __syncthreads();
-    return !r.fail;
+    return !(r.fail[0] | r.fail[1]);   // next set behind the barrier after the solve
 }
 
 // A member's share of an iteration of the tracking kernel (members are
@@ -1027,10 +1031,10 @@ __device__ inline bool take_pose(const unsigned long long* pub, const unsigned* 
         if (ok)
             reinterpret_cast<unsigned*>(pose)[threadIdx.x] = (unsigned)(x >> 32);
         else
-            r.fail = 1;
+            r.fail[0] = 1;
     }
     __syncthreads();
-    return !r.fail;
+    return !r.fail[0];   // next set behind store_partial's barrier
 }
 
 // Work-groups that take part at a level: about kPixPerGroup pixels each,
@@ -1114,7 +1118,7 @@ __global__ __launch_bounds__(kTrackBlock) void k_track_frame(MapView M, TrackArg
     // costs one load)
     const bool leader = xcd_leader(b);
     if (threadIdx.x == 0) {
-        red.fail = 0;
+        red.fail[0] = red.fail[1] = 0;
         if (leader)
             __hip_atomic_store(&sync[kSyncXcc + xcd_leaf(b)], xcc_id() + 1u, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
@@ -1244,7 +1248,7 @@ __global__ __launch_bounds__(kTrackBlock) void k_track_frame(MapView M, TrackArg
             }
             __syncthreads();
             // by another wave than the one that solves (red.tot is next
-            // written after two more barriers)
+            // written behind the barrier of the next store_partial)
             if (counts) {
                 const double* t = red.tot;
                 if (l == 0 && it == a.iters[0] - 1 && t[28] < (double)a.min_inlier_frac * t[29])
