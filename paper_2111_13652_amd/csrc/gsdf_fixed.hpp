@@ -1,22 +1,31 @@
-// Fixed-point terms of the per-frame voxel sums of fusion (Eq. (1)-(3)).
+// Fixed-point terms of the voxel sums of fusion (a frame's, Eq. (1)-(3)) and
+// of the adjoint.  Integer sums are exact, so they do not depend on the order
+// of their terms, and a total is rounded once, to float (from_fixed).
 //
-// A term w x enters as (w 2^f) x: scaling by a power of two is exact, so
-// this is (w x) 2^f rounded once.  The 64-bit integer is formed from two
-// 32-bit conversions, hi = floor(w x 2^(f-32)) and lo = w x 2^f - hi 2^32
-// (one instruction each, where a direct 64-bit conversion is a long
-// sequence).  For w x >= 0, and for w x <= -2^(32-f) (whose float32 value
-// is a multiple of 2^9 units), the remainder lo is exact and lies in
-// [0, 2^32).  A negative term smaller than that in magnitude leaves a
-// remainder 2^32 - |w x 2^f| that can need more than 24 bits; lo is then
-// rounded to the nearest float, at most 2^7 units away, and may round up to
-// exactly 2^32, where the conversion saturates to 2^32 - 1 (one unit below
-// the carry it stands for, again within 2^7).  So a term is exact unless it
-// is below 2^(23-f) or a negative one below 2^(32-f) in magnitude, which is
-// rounded, deterministically, within 2^(7-f).  Integer sums are exact and
-// the total is rounded once, to float.  ws = w 2^f, wh = w 2^(f-32).
+// The kernels form a term w x by magic_term: t = fma(w, x, M) with
+// M = 1.5 * 2^(52-f) holds w x, rounded once to a multiple of 2^-f, in its low
+// mantissa bits (a float64 of that magnitude has no finer digits), so the
+// 64-bit difference of t's and M's bit patterns is the integer w x 2^f.  The
+// float64 product of two floats is exact; a term costs an fma and a 64-bit
+// addition.  A term must stay below 2^51 units, |w x| < 2^(51-f), a sum below
+// 2^63, and w x must be a number (the bits of a NaN or an infinity are an
+// arbitrary integer).
 //
-// Everything here is plain arithmetic on host and device, so a host unit
-// test exercises the same functions the fusion kernel calls.
+// fixed_term is the form it replaced, which no kernel uses and the host tests
+// keep as its comparison: the float32 product in units of 2^-f, split into
+// hi = floor(w x 2^(f-32)) and lo = w x 2^f - hi 2^32, which needs only a sum
+// below 2^63 but six instructions.  Its terms are exact unless below 2^(23-f)
+// or negative ones below 2^(32-f) in magnitude, where lo is rounded, within
+// 2^(7-f) (2^32 itself saturates to 2^32 - 1).  The limit on a term costs
+// magic_term fraction bits (fusion at 640x480 and 1 cm 50 where there were 52,
+// the adjoint up to 11 in blocks of few pixels), the float32 product costs
+// fixed_term more.  Errors of a voxel's sum against exact ones, rms over
+// random frames: fusion 1.6e-9 m there, 6e-16 here at 2 cm voxels,
+// 9e-10 and 1e-15 at 1 cm; the adjoint's offset sums 1e-13 and 1e-20 of a
+// block of eight pixels with residuals of 3 mm.
+//
+// Everything here is plain arithmetic on host and device, so host unit tests
+// exercise the functions that the kernels call.
 #pragma once
 
 #include <cmath>
@@ -46,12 +55,6 @@ __host__ __device__ inline unsigned long long fixed_term(float ws, float wh, flo
     return ((unsigned long long)(uint32_t)(int32_t)hs << 32) | (unsigned long long)sat_u32(lo);
 }
 
-// The same sums with terms formed in float64: t = fma(w, x, M) with
-// M = 1.5 * 2^(52-f) holds w x, rounded once to a multiple of 2^-f, in its low
-// mantissa bits (a float64 of that magnitude has no finer digits), so the
-// 64-bit difference of t's and M's bit patterns is the integer w x 2^f.  
-// |w x| < 2^(51-f).  A term costs an fma and a 64-bit addition (fixed_term:
-// six instructions), and the float64 product of two floats is exact.
 __host__ __device__ inline double magic_of(int f) { return ldexp(1.5, 52 - f); }
 
 __host__ __device__ inline unsigned long long double_bits(double t) {
