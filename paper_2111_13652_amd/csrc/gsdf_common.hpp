@@ -146,7 +146,13 @@ struct AuxLayout {
 // 44 ns on one address).
 constexpr int kFuseTeams = 8;
 constexpr int kMaxParts = 8;
-constexpr int kTeamBuffers = 256;               // partial-sum buffers of a team's split blocks
+// Partial-sum buffers of a team's split blocks.  A piece stands for at least a
+// 128th of the team's pixels and a split block for more than one piece, so the
+// blocks' shares add up to at most 128, split blocks are fewer than that and
+// their parts, each share rounded up, fewer than 256.  (Counts that added up
+// over very many allocations may wrap in the team's sum and ask for more: the
+// blocks beyond the buffers stay whole.)
+constexpr int kTeamBuffers = 256;
 constexpr int kTouchedMost = 1 << 30;           // a count takes no more from there on (see mark_touched)
 __host__ __device__ inline size_t touched_slots(size_t nb) { return (nb + 511) / 512 * 512; }   // whole chunks of every team
 
