@@ -186,7 +186,7 @@ int gsdf_allocate_blocks(gsdf_map* map, const float* depth_dev, const gsdf_camer
 
 /* Scratch bytes gsdf_integrate_frame uses for `cam`: one float4 per pixel
  * (rounded up to 256 bytes), then room for the partial sums of blocks that
- * are fused in several parts.  With the pixels' share alone the call gives
+ * are fused in several parts (40 MiB for every camera).  With the pixels' share alone the call gives
  * the same result, every block fused by one work-group (slower where
  * surfaces are near the camera); with less it returns GSDF_EINVAL. */
 size_t gsdf_integrate_scratch_bytes(const gsdf_camera* cam);
@@ -324,7 +324,12 @@ int gsdf_compose_poses(int32_t n, const double* T0_dev, const double* xi_dev, do
 /* Scratch bytes of gsdf_keyframe_loss / gsdf_backward for K keyframes and
  * a parameter buffer of param_blocks rows (scratch sized for the map's
  * max_blocks serves every param_blocks).  0 when the arguments are invalid
- * or K x W x H exceeds INT32_MAX (pixels are numbered in int32). */
+ * or K x W x H exceeds INT32_MAX (pixels are numbered in int32).  The last
+ * part of it, up to 64 MiB, holds the partial sums of blocks that
+ * gsdf_backward gathers in several parts: with less than the whole the two
+ * calls give the same results, every block gathered by one work-group (slower
+ * where surfaces are near the camera), and without even what comes before
+ * that part they return GSDF_EINVAL. */
 size_t gsdf_keyframe_scratch_bytes(const gsdf_camera* cam, int32_t n_keyframes, int64_t param_blocks);
 
 /* Keyframe loss (Sec. 4.1 Eq. (5), (14); Huber penalty of Sec. 5.1): for
@@ -341,7 +346,7 @@ size_t gsdf_keyframe_scratch_bytes(const gsdf_camera* cam, int32_t n_keyframes, 
  *     reads them instead of searching (for finite differences);
  *   loss_dev: K float64 (device); count_dev (optional): K float64 pixels used.
  * Errors: GSDF_EINVAL for bad sizes, null buffers, freeze without assoc or
- * scratch smaller than gsdf_keyframe_scratch_bytes(cam, K, param_blocks). */
+ * too small a scratch (see gsdf_keyframe_scratch_bytes). */
 int gsdf_keyframe_loss(const gsdf_map* map, const float* depth_dev, int32_t n_keyframes,
                        const gsdf_camera* cam, const double* T0_dev, const double* xi_dev,
                        const float* params_dev, int64_t param_blocks, float huber_delta,

@@ -49,9 +49,8 @@ constexpr int kFuseChunk = 1536;   // box pixels scanned per pass (LDS queue cap
 constexpr int kScanBatch = 2;      // box pixels a thread of the scan looks at together
 constexpr int kTeamGroups = 128;   // work-groups of a team: four a CU over the eight teams
 constexpr int kClasses = 4;        // order of a team's pieces: parts of split blocks, then whole ones, long to short
-constexpr float kPieceShare = 1.0f;   // of a member's part of the pixels, to a piece
 constexpr int kPiecePixels = 256;  // shortest part of a split block, in pixels whose band meets the block
-constexpr int kSortBins = 32;      // queue entries are sorted by their number of band samples, 31 or more alike
+constexpr int kSortBins = 32;      // queue entries are sorted by their number of band samples, 32 or more alike
 constexpr float kBoxMargin = 1e-4f;  // metres; far above binary32 rounding of coordinates
 
 struct FuseConsts {
@@ -452,7 +451,7 @@ __global__ __launch_bounds__(kFuseBlock, 4) void k_fuse_blocks(MapView M, const 
     sum = 0;
 #pragma unroll
     for (int w = 0; w < kFuseBlock / 64; ++w) sum += s_sum[w];
-    const float inv_target = 1.0f / fmaxf((float)kPiecePixels, (float)sum * (kPieceShare / kTeamGroups));
+    const float inv_target = 1.0f / fmaxf((float)kPiecePixels, (float)sum * (1.0f / kTeamGroups));
 #pragma unroll 1
     for (int j = my_chunk; j < team_chunks; j += kPerStep) {
         const int4 v = j == my_chunk ? ahead : counts_of(j);
@@ -969,8 +968,9 @@ inline FuseConsts fuse_consts(const gsdf_map& map, const gsdf_camera& cam, const
 }
 
 // Scratch of the fusion calls: {n_w, D} per pixel, then the partial sums of
-// the parts of split blocks.  A caller that brings the pixels' share alone
-// has every block fused whole.
+// the parts of split blocks (40 MiB whatever the camera: the most parts that a
+// frame can have).  A caller that brings the pixels' share alone has every
+// block fused whole.
 inline size_t pix_bytes(const gsdf_camera& cam) { return align256((size_t)cam.width * cam.height * sizeof(float4)); }
 constexpr size_t kPartsBytes =
     (size_t)kFuseTeams * kTeamBuffers * 5 * kBlockVoxels * sizeof(unsigned long long);
