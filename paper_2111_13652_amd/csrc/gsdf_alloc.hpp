@@ -17,7 +17,8 @@ constexpr int kAllocSet = 1024;  // LDS set capacity (keys) per tile
 // and marked as touched by this frame, by about the number of the tile's
 // pixels whose band meets the block (s_px).  Every thread of the 256-thread
 // work-group must call it (it synchronises); red holds 4 words of LDS.
-template <bool ADD_UP>
+// ALONE: the launch is allocation's own, and fusion need not follow it.
+template <bool ALONE>
 __device__ inline void allocate_tile(const MapView& M, const float* __restrict__ depth, int W, int H, float zmin,
                                      float zmax, const BandConsts& bc, const double* __restrict__ Twc,
                                      int32_t* status, int tu, int tv, unsigned long long* s_keys,
@@ -71,11 +72,14 @@ __device__ inline void allocate_tile(const MapView& M, const float* __restrict__
             if (!placed) {  // set full: go to the global table directly
                 int created;
                 const int32_t slot = hash_insert(M, bx, by, bz, status, &created);
-                if (slot >= 0) mark_touched<ADD_UP>(M, slot, 1);
+                if (slot >= 0) mark_touched(M, slot, 1, !ALONE);
             }
         }
     }
+    // calls of allocation alone since the last fusion
+    const int pending = ALONE ? M.counters[kPending] : 0;
     __syncthreads();
+    const bool add = pending < 3;
     unsigned long long probes = 0;
     for (int i = threadIdx.x; i < kAllocSet; i += blockDim.x) {
         const unsigned long long key = s_keys[i];
@@ -84,11 +88,12 @@ __device__ inline void allocate_tile(const MapView& M, const float* __restrict__
         unpack_key(key, &bx, &by, &bz);
         // the inserting thread marks a new block; others mark known slots
         const int32_t slot = hash_insert(M, bx, by, bz, status, &created);
-        if (slot >= 0) mark_touched<ADD_UP>(M, slot, max(s_px[i], 1));
+        if (slot >= 0) mark_touched(M, slot, max(s_px[i], 1), add);
         ++probes;
     }
     probes = block_sum_u64(probes, red);
     if (threadIdx.x == 0) add_stat(M, kStatAllocPairs, probes);
+    if (ALONE && tu == 0 && tv == 0 && threadIdx.x == 0 && add) atomicAdd(&M.counters[kPending], 1);
 }
 
 }  // namespace gsdf

@@ -149,14 +149,13 @@ constexpr int kMaxParts = 8;
 // Partial-sum buffers of a team's split blocks.  A piece stands for at least a
 // 128th of the team's pixels and a split block for more than one piece, so the
 // blocks' shares add up to at most 128, split blocks are fewer than that and
-// their parts, each share rounded up, fewer than 256.  (Counts that added up
-// over very many allocations may wrap in the team's sum and ask for more: the
-// blocks beyond the buffers stay whole.)
+// their parts, each share rounded up, fewer than 256.  (A sum that wrapped,
+// above some fifty megapixels, may ask for more: the blocks beyond the buffers
+// stay whole.)
 constexpr int kTeamBuffers = 256;
-constexpr int kTouchedMost = 1 << 30;           // a count takes no more from there on (see mark_touched)
 __host__ __device__ inline size_t touched_slots(size_t nb) { return (nb + 511) / 512 * 512; }   // whole chunks of every team
 
-enum Counter { kNumBlocks = 0, kTeamTicket = 64, kTeamDone = kTeamTicket + kFuseTeams * 16,
+enum Counter { kNumBlocks = 0, kPending = 32, kTeamTicket = 64, kTeamDone = kTeamTicket + kFuseTeams * 16,
                kCounterWords = kTeamDone + kFuseTeams * 16 };
 
 // Work counters are striped over kStatStripes addresses (work-group b adds
@@ -410,13 +409,16 @@ __device__ inline unsigned long long wave_sum_u64(unsigned long long x) {
 // Record that `pixels` more pixels of the current frame touch a block (the
 // fusion kernel that consumes the count runs later): a device-scope atomic
 // without a return, so nothing waits for it.  The counts end with the fusion
-// that consumes them; allocation alone (ADD_UP) may be called any number of
-// times before one, so it stops adding at kTouchedMost, to which a frame adds
-// less than as much again.
-template <bool ADD_UP>
-__device__ inline void mark_touched(const MapView& M, int32_t slot, int pixels) {
-    if (ADD_UP && M.touched[slot] >= kTouchedMost) return;
-    __hip_atomic_fetch_add(&M.touched[slot], pixels, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// that consumes them, but allocation alone may be called any number of times
+// before one: from the third call on (kPending) it only raises a count to
+// `pixels` (`add` false), so that three frames of at most 2^28 pixels bound it.
+// (A look at the count before an addition waits for the additions of other
+// tiles: allocation 19.5 -> 27 us at 640x480.)
+__device__ inline void mark_touched(const MapView& M, int32_t slot, int pixels, bool add) {
+    if (!add)
+        __hip_atomic_fetch_max(&M.touched[slot], pixels, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        __hip_atomic_fetch_add(&M.touched[slot], pixels, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Sum over a work-group (every thread passes its value; thread 0 gets the

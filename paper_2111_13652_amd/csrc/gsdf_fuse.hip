@@ -437,8 +437,8 @@ __global__ __launch_bounds__(kFuseBlock, 4) void k_fuse_blocks(MapView M, const 
     for (int i = threadIdx.x; i < kClasses * 65; i += kFuseBlock) (&s_pre[0][0])[i] = 0;
     // pixels to a piece: the share of a member, so that a frame whose blocks
     // are few or uneven still fills the chip
-    // (counts of very many allocations may wrap in the sum: it sizes the
-    // pieces, the result does not depend on it)
+    // (a sum that wrapped, above some fifty megapixels, gives other pieces and
+    // the same result)
     int sum = ahead.x + ahead.y + ahead.z + ahead.w;
 #pragma unroll 1
     for (int j = my_chunk + kPerStep; j < team_chunks; j += kPerStep) {
@@ -907,6 +907,7 @@ __global__ __launch_bounds__(kFuseBlock, 4) void k_fuse_blocks(MapView M, const 
         for (int j = wave; j < team_chunks; j += kFuseBlock / 64)
             M.touched[(j * kFuseTeams + team) * 64 + lane] = 0;
         if (threadIdx.x == 0) {
+            if (team == 0) M.counters[kPending] = 0;   // (no other member reads it)
             __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_store(&M.counters[kTeamDone + team * 16], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
