@@ -49,7 +49,7 @@ constexpr int kFuseChunk = 1536;   // box pixels scanned per pass (LDS queue cap
 constexpr int kScanBatch = 2;      // box pixels a thread of the scan looks at together
 constexpr int kTeamGroups = 128;   // work-groups of a team: four a CU over the eight teams
 constexpr int kClasses = 4;        // order of a team's pieces: parts of split blocks, then whole ones, long to short
-constexpr int kPiecePixels = 256;  // shortest part of a split block, in pixels whose band meets the block
+constexpr int kPiecePixels = 1024;   // shortest part of a split block, in pixels whose band meets the block
 constexpr int kSortBins = 32;      // queue entries are sorted by their number of band samples, 32 or more alike
 constexpr float kBoxMargin = 1e-4f;  // metres; far above binary32 rounding of coordinates
 
@@ -380,9 +380,14 @@ __device__ inline FuseItem find_item(const MapView& M, int team, int chunks, flo
 // counters and 3 us on each slot without work, and where surfaces are near
 // the camera a few blocks ran long after the rest.  Event times, three views
 // each: 640x480 FP32 139 / 79 / 87 -> 75 / 66 / 67 us; 1280x720 BF16
-// 238 / 185 / 199 -> 153 / 149 / 148 us; 213x157 without gradients
-// 48 / 30 / 26 -> 34 / 29 / 31 us (the 5 us in which the members count the
-// team's pieces show there).  Sorting the queue by the number of samples:
+// 238 / 185 / 199 -> 153 / 149 / 148 us.  Small frames gain the least (the 5 us
+// in which the members count the team's pieces show there), and lose where
+// parts are short: a part stores, waits for and adds 20 KB of sums.  With
+// kPiecePixels of 256, 512, 1024, 2048 the frame call takes 43.5, 36.7, 36.3,
+// 37.0 us at 160x120 and 42.6, 40.8, 36.6, 38.0 at 213x157 without gradients
+// (38.4 and 43.1 with one work-group to a block), and with a plane at 0.45 m
+// 77, 68, 62, 70 at 160x120 and 60, 62, 54, 62 at 213x157 (127 and 183); from
+// 640x480 on the four are alike, as a member's share is larger.  Sorting the queue by the number of samples:
 // 640x480 137 / 90 / 98 -> 110 / 80 / 89 us before the pieces were even.
 template <int STORAGE>
 __global__ __launch_bounds__(kFuseBlock, 4) void k_fuse_blocks(MapView M, const float4* __restrict__ pix,

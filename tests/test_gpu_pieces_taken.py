@@ -27,8 +27,13 @@ def _cam(width, height):
     return synth.Camera(f, f, (width - 1) / 2, (height - 1) / 2, width, height, 0.3, 4.0)
 
 
-@pytest.mark.parametrize("width,height,z,split", [(640, 480, 0.45, True), (333, 251, 0.6, True), (40, 30, 2.0, False)])
-def test_fusion_uses_its_buffers(width, height, z, split):
+@pytest.mark.parametrize("storage,width,height,z,split", [
+    ("fp32", 640, 480, 0.45, True),
+    ("nograd", 333, 251, 0.4, True),
+    ("fp32", 333, 251, 0.6, True),
+    ("bf16", 40, 30, 2.0, False),
+])
+def test_fusion_uses_its_buffers(storage, width, height, z, split):
     import torch
     from paper_2111_13652_amd import _lib
     from paper_2111_13652_amd.gsdf import COS_75, GsdfMap, camera
@@ -36,16 +41,26 @@ def test_fusion_uses_its_buffers(width, height, z, split):
     lib, c = _lib.load(), camera(cam)
     full = lib.gsdf_integrate_scratch_bytes(C.byref(c))
     pixels = -(-width * height * 16 // 256) * 256
-    scratch = torch.full((full,), 0xA5, dtype=torch.uint8, device="cuda")
-    m = GsdfMap(0.01, 0.05, 8192)
     D, pose = dev(_plane(cam, z, np.random.default_rng(1))), dev(EYE)
     p = _lib.FuseParams(0.01, COS_75)
-    _lib.check(lib.gsdf_fuse_frame(C.byref(m._map), D.data_ptr(), C.byref(c), pose.data_ptr(), C.byref(p),
-                                   scratch.data_ptr(), full, m.status.data_ptr(), None), "fuse_frame")
-    torch.cuda.synchronize()
-    used = bool((scratch[pixels:] != 0xA5).any())
-    log(f"case: {width}x{height} at {z} m: {m.num_blocks()} blocks, buffers used: {used}")
-    assert m.status_flags() == [] and used == split
+    maps = []
+    for size in (full, pixels):
+        scratch = torch.empty((full,), dtype=torch.uint8, device="cuda")
+        m = GsdfMap(0.01, 0.05, 8192, storage=storage)
+        for _ in range(2):   # the first frame's blocks count few pixels: their slots are not known yet
+            scratch.fill_(0xA5)
+            _lib.check(lib.gsdf_fuse_frame(C.byref(m._map), D.data_ptr(), C.byref(c), pose.data_ptr(), C.byref(p),
+                                           scratch.data_ptr(), size, m.status.data_ptr(), None), "fuse_frame")
+        torch.cuda.synchronize()
+        used = bool((scratch[pixels:] != 0xA5).any())
+        log(f"case: {storage} {width}x{height} at {z} m: {m.num_blocks()} blocks, buffers used: {used}")
+        assert m.status_flags() == [] and used == (split and size == full)
+        keys = m.keys()
+        o = np.lexsort(keys.T[::-1])
+        maps.append([keys[o]] + [x[o] for x in m.voxels(len(keys))])
+    assert maps[0][3].max() > 0
+    for a, b in zip(*maps):
+        assert np.array_equal(a, b)
 
 
 @pytest.mark.parametrize("width,height,K,split", [(320, 240, 3, True), (40, 30, 1, False)])
