@@ -480,7 +480,12 @@ __global__ __launch_bounds__(kAdjBlock, FREEZE ? 4 : 5) void k_adj_pixels(MapVie
         t[r] = poses[12 * kf + 4 * r + 3];
     }
     const float s = gscale[kf];
-    const bool finite = pose_finite(poses + 12 * kf);   // uniform over the work-group
+    // uniform over the work-group; no branches, the lookups need not wait
+    bool finite = true;
+#pragma unroll
+    for (int r = 0; r < 9; ++r) finite &= isfinite(R[r]);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) finite &= isfinite(t[r]);
     const int N = a.W * a.H;
     const float* dimg = depth + (size_t)kf * N;
     const int32_t* aimg = FREEZE ? assoc + (size_t)kf * N * 3 : nullptr;
