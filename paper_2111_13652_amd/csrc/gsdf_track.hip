@@ -1048,9 +1048,11 @@ constexpr int kMinGroups = 128;
 // (b mod 8 = 0), each of which adds all of their partials itself: one hop
 // through that XCD's L2 (0.46 us) instead of two hops, the second between
 // XCDs (1.2 us).  Above it the pixels' own time on 32 CUs outgrows what the
-// hop saves: an iteration takes 3.4 us against 5.0 at 1200 pixels, 4.5
-// against 5.0 at 19200, and at 57600 would take three pixels a thread more
-// where the whole grid takes 5.2.  The plain Taylor form only (`one`): the compensated sums keep
+// hop saves.  An iteration on one XCD and on the whole grid takes 3.5 and 4.9
+// us at 1200 pixels, 4.3 and 5.05 at 19200, 4.35 and 5.0 at 24576, 4.7 and 5.0
+// at 32448, 5.5 and 5.1 at 43200, 7.0 and 5.2 at 76800: the line lies well
+// before the two meet, where a thread still holds at most two pixels.  The
+// plain Taylor form only (`one`): the compensated sums keep
 // their grouping, and the tri-linear form's pixels cost several times as
 // much.  Where some levels go to one XCD the others take the whole grid, so
 // that every work-group of a level is also in the next one: a work-group
