@@ -117,15 +117,15 @@ __device__ inline bool photo_project(const PhotoArgs& a, const double* T, const 
     for (int r = 0; r < 3; ++r) P->x[r] = T[r] * d[0] + T[4 + r] * d[1] + T[8 + r] * d[2];
     P->z = P->x[2];
     if (!(P->z >= a.zmin)) return false;
-    // one reciprocal (hardware estimate and two Newton steps: within an ulp)
-    // for both quotients and the gradient's 1 / z.  The quotients decide
-    // visibility (image border, nearest pixel), so each is corrected by its
-    // exact remainder (Markstein, IBM J. Res. Dev. 34, 1990) to the rounding
-    // of a division: uncorrected, points exactly on column 0 fall outside.
+    // one reciprocal (hardware estimate and a Newton step, about 2^-44) for
+    // both quotients, a second step for the gradient's 1 / z.  The quotients
+    // decide visibility (image border, nearest pixel), so each is corrected by
+    // its remainder (Markstein, IBM J. Res. Dev. 34, 1990), to 2^-88 before
+    // its last rounding: a division's result, and exact where that is exact.
+    // (Uncorrected, points exactly on column 0 fall outside.)
     double iz = __builtin_amdgcn_rcp(P->z);
     iz = fma(iz, fma(-P->z, iz, 1.0), iz);
-    iz = fma(iz, fma(-P->z, iz, 1.0), iz);
-    P->iz = iz;
+    P->iz = fma(iz, fma(-P->z, iz, 1.0), iz);
     P->u = quotient(a.fx * P->x[0], P->z, iz) + a.cx;
     P->v = quotient(a.fy * P->x[1], P->z, iz) + a.cy;
     if (!(P->u >= 0.0 && P->u < (double)(a.W - 1) && P->v >= 0.0 && P->v < (double)(a.H - 1))) return false;
