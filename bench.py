@@ -67,10 +67,10 @@ B_ALLOC_PAIR = 16.0
 # values they had when the counters were taken.
 MEASURED_TRAFFIC = {
     "track": {
-        "bytes": 11198173,
+        "bytes": 11155025,
         "sources": {
-            "gsdf_track.hip": "872ea7dce32d23801993d1cff8f4318ebacb8f5230eee12c44598b965dc3180d",
-            "gsdf_common.hpp": "ec15729877f4ad6f003f0015a7e4bda6b8dc9f641389eb54ead8af9273a9c1c9",
+            "gsdf_track.hip": "e4fbe169d614de28c802d95de4cfc81ba999adcec34e9aa8b6a5a106c1b89f4b",
+            "gsdf_common.hpp": "b6cc458c6eb09c9529a7f7eb6808922beaeeed1eb822e5e1122d7ad1fe1fd5dc",
             "gsdf_host.hpp": "699a644f6155d591caffb7f5edc3cd6c971c32bc580d070b327d1d31c947ff6e",
             "gsdf_se3.hpp": "13c15ea94701e1129da7175cf338be9aa9cc57bf8857172577cef813f6209733"
         }

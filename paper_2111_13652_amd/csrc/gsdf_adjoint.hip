@@ -450,8 +450,8 @@ __device__ inline void block_scan2(int32_t a, int32_t b, int32_t* ex_a, int32_t*
 // pixel changed nothing).  The sums across lanes and the scans by register
 // moves instead of shuffles, the voxel kept in float64 and the shorter hash
 // and Morton code: 30 keyframes of 640x480 122 -> 82 us, 88 with the records'
-// places (which take 11 us from k_adj_runs).  95 registers hold five waves
-// to a SIMD; the frozen form takes four.
+// places (which take 11 us from k_adj_runs), 92 with the check of the pose.
+// 95 registers hold five waves to a SIMD; the frozen form takes four.
 template <bool FREEZE>
 __global__ __launch_bounds__(kAdjBlock, FREEZE ? 4 : 5) void k_adj_pixels(MapView M, AdjArgs a, const float* __restrict__ depth,
                                                           const double* __restrict__ poses,
