@@ -69,7 +69,7 @@ MEASURED_TRAFFIC = {
     "track": {
         "bytes": 11155025,
         "sources": {
-            "gsdf_track.hip": "e4fbe169d614de28c802d95de4cfc81ba999adcec34e9aa8b6a5a106c1b89f4b",
+            "gsdf_track.hip": "6936899bd1332983ac1fba726f6089dec221e6530248513d8e087239df2cd5bb",
             "gsdf_common.hpp": "b6cc458c6eb09c9529a7f7eb6808922beaeeed1eb822e5e1122d7ad1fe1fd5dc",
             "gsdf_host.hpp": "699a644f6155d591caffb7f5edc3cd6c971c32bc580d070b327d1d31c947ff6e",
             "gsdf_se3.hpp": "13c15ea94701e1129da7175cf338be9aa9cc57bf8857172577cef813f6209733"

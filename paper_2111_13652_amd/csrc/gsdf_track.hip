@@ -472,10 +472,10 @@ __device__ inline void accumulate_trilinear(const MapView& M, const TrackLevel& 
 // 40 times further from the float64 oracle's.  A float32 sum of four threads
 // that hold two pixels each spans eight pixels and does the same, so a one-XCD
 // level, whose threads hold two, adds every thread's values in float64 (WIDE;
-// 1.9 us a launch of 19 iterations at 160x120).  The sphere, 160x120, 24
-// starts: rotation after one iteration 5.1e-7 rad rms from the oracle's in
-// fours, 1.7e-7 wide (6.0e-7 in fours of single pixels); centre after ten, in
-// the median, 1.4e-7 m, 6e-9 wide (9e-8).  The precision form
+// 1.9 us a launch of 19 iterations at 160x120).  The sphere, 160x120, 240
+// starts, ten iterations: the centre's median distance from the oracle's is
+// 2.0e-7 m in fours, 3.2e-9 wide (1.3e-7 in fours of single pixels), 69 and
+// 34 of them lie above 1e-6 m (58).  The precision form
 // (COMP) uses compensated float32 at every stage: 8 threads per entry, two
 // chunks each, then the first kNE threads add the 8 parts.
 //
